@@ -49,8 +49,8 @@ FLOP_AXIS = 4 * 32 + 59
 FLOP_POINTWISE = 4           # rho += f psi^2, V psi
 
 
-VARIANT_NAMES = {0: "pass-by-pass", 1: "plane-resident (vector FMA)",
-                 2: "plane-resident (float64 matrix cores)",
+VARIANT_NAMES = {0: "pass-by-pass", 1: "plane-resident",
+                 2: "plane-resident (float64)",
                  3: "exact int8 digit products on the matrix cores (plane-resident)"}
 NCAND = 15      # tuner candidates: 5 launch sequences x 3 tile shapes
 
@@ -63,7 +63,7 @@ def stage_model(stage, prec, variant):
     operation count for the axes the stage covers."""
     es = ESIZE[prec]
     if stage == "xy_plane":
-        bound = "mfma" if ((prec == "f64" and variant == 2) or variant == 3) else "alu"
+        bound = "mfma" if variant == 3 else "alu"
         return bound, 4 * es, 2 * FLOP_AXIS + FLOP_POINTWISE
     if stage == "z_final":       # t, c, kxy in; H*psi out
         return "hbm", 4 * es, None
@@ -82,7 +82,7 @@ def stage_model(stage, prec, variant):
 
 # the sources each profiled kernel is built from
 STAGE_SOURCES = {
-    "xy_plane": ["wvl_xy.hip", "wvl_xy_impl.h", "wvl_xy_mf_sh.hip", "wvl_plane.h", "wvl_kernels.h",
+    "xy_plane": ["wvl_xy.hip", "wvl_line.h", "wvl_line_f64_sh.hip", "wvl_plane.h", "wvl_kernels.h",
                  "wvl_internal.h", "filters_gen.h"],
 }
 
@@ -402,7 +402,7 @@ def run_uneven(steps, warmup):
     tm = (ctypes.c_double * NCAND)()
     lib.wvl_plan_tuning(plan.h, ctypes.byref(v), tm, NCAND)
     pts = int(sum(np.prod(inputs.fine_shape(d)) for d in dims))
-    seqs = ["pass_by_pass", "plane_occ4", "plane_occ2", "plane_vector_engine", "exact_products"]
+    seqs = ["pass_by_pass", "plane", "plane_workgroup_wide", "plane_workgroup_wide_vector", "exact_products"]
     shapes = ["default_tiles", "half_axis1_tiles", "persistent_4_per_cu"]
     names = [f"{a}/{b}" for a in seqs for b in shapes]
     best = plan.query(lib.WVL_Q_TUNE_BEST)

@@ -23,10 +23,16 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-ffp-contract=
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-munsafe-fp-atomics", "-Wall", "-Wno-unused-function",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+# The plane kernel's filter coefficients are constants in scalar registers;
+# hoisting them out of the loop over a group's orbitals would spill them.
+LINE_FLAGS = ["-mllvm", "-disable-machine-licm"]
 
 
 def sources():
-    return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
+    # the plane kernels take longest to compile: first
+    fs = sorted((f for f in os.listdir(CSRC) if f.endswith(".hip")),
+                key=lambda f: (not f.startswith("wvl_line_"), f))
+    return [os.path.join(CSRC, f) for f in fs]
 
 
 def _headers():
@@ -41,7 +47,7 @@ def _compile(src, incremental=False):
         t = os.path.getmtime(obj)
         if all(os.path.getmtime(d) < t for d in [src] + _headers()):
             return obj, ""
-    cmd = [HIPCC] + FLAGS + ["-c", src, "-o", obj]
+    cmd = [HIPCC] + FLAGS + (LINE_FLAGS if os.path.basename(src).startswith("wvl_line_") else []) + ["-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")

@@ -18,6 +18,7 @@
 
 #include "wvl.h"
 #include "wvl_kernels.h"
+#include "wvl_plane.h"
 
 using namespace wvl;
 
@@ -108,6 +109,10 @@ struct wvl_plan {
   bool xy_ok = false;    // some form of the plane path fits (workspace reserved)
   int xy_m1 = 0, xy_m2 = 0, xy_G = 1, xy_ngroups = 0, xy_blocks = 0, xy_occ = 4;
   int xy_engine = 0;   // in-plane passes: 0 vector FMA, 1 float64 matrix cores
+  // classes of orbitals with one launch shape of the plane kernel (wvl_line.h),
+  // as ranges of perm_q / order_q; none if some plane is too large for it
+  struct LineClass { int first, n, m1, m2, tiles; };
+  std::vector<LineClass> line_cls;
   bool zfuse = true;   // last two z passes of the plane path fused (not for F32C)
   // exact-product engine of the compensated form (uniform batches with a
   // shared potential, lengths multiples of 16, isotropic grid spacing)
@@ -501,8 +506,25 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
       for (int r = 0; r < norb; ++r) order[r + 1] = order[r] + (pre[perm[r] + 1] - pre[perm[r]]);
     };
     build(p->perm_z, p->order_z, p->pz, [&](int b) { return (int64_t)p->orbs[b].m[2]; });
-    build(p->perm_q, p->order_q, p->pq,
-          [&](int b) { return (int64_t)p->orbs[b].m[0] * p->orbs[b].m[1]; });
+    // (planes: by launch shape of the plane kernel first)
+    auto shape = [&](int b) { return line_shape_of(prec, p->orbs[b].m[0], p->orbs[b].m[1]); };
+    build(p->perm_q, p->order_q, p->pq, [&](int b) {
+      return ((int64_t)(shape(b) + 1) << 40) + (int64_t)p->orbs[b].m[0] * p->orbs[b].m[1];
+    });
+    for (int r = 0; r < norb; ++r) {
+      const int b = p->perm_q[r], sh = shape(b);
+      if (sh < 0) { p->line_cls.clear(); break; }
+      if (r == 0 || sh != shape(p->perm_q[r - 1])) p->line_cls.push_back({r, 0, 0, 0, 0});
+      auto& k = p->line_cls.back();
+      ++k.n;
+      k.m1 = std::max(k.m1, p->orbs[b].m[0]);
+      k.m2 = std::max(k.m2, p->orbs[b].m[1]);
+      k.tiles = p->order_q[r + 1] - p->order_q[k.first];
+    }
+    // the largest lengths of a class may come from different orbitals: such a
+    // plane has to fit a shape too
+    for (const auto& k : p->line_cls)
+      if (line_shape_of(prec, k.m1, k.m2) < 0) { p->line_cls.clear(); break; }
     // pass-by-pass sequence: y tiles cost ~ m2, x tiles ~ their rows x m1,
     // pointwise tiles are all alike
     build(p->perm_y, p->order_y, p->py, [&](int b) { return (int64_t)p->orbs[b].m[1]; });
@@ -934,7 +956,7 @@ int hpsi_oz(wvl_plan* p, hipStream_t st, const void* c, const double* V, double 
   }
   if (rho || want_e) {
     Mark mk(p, st, ST_RHO);
-    WVL_CHK(launch_rho_reduce(rhop, p->xy_ngroups, p->M, V, rho, want_e ? rv : nullptr, st));
+    WVL_CHK(launch_rho_reduce(rhop, p->xy_ngroups, p->M, V, rho, 0, want_e ? rv : nullptr, st));
   }
   {
     Mark mk(p, st, ST_ZFIN);
@@ -951,18 +973,64 @@ int hpsi_oz(wvl_plan* p, hipStream_t st, const void* c, const double* V, double 
   return WVL_OK;
 }
 
+// whether the in-plane part runs in the plane kernel of wvl_line.h
+bool use_line(const wvl_plan* p) {
+  return p->xy_occ == 4 && (p->prec != WVL_F64 || p->xy_engine == 1) && !p->line_cls.empty();
+}
+
+// arguments of the in-plane kernels that do not depend on the call
+XyArgs xy_args(const wvl_plan* p, void* ws) {
+  XyArgs a{};
+  a.orbs = p->d_orbs;
+  a.pq = p->d_pq;
+  a.norb = p->norb;
+  a.shared = p->shared ? 1 : 0;
+  a.ngroups = p->xy_ngroups;
+  a.G = p->xy_G;
+  a.M = p->M;
+  a.plane = p->elems;
+  a.pot_scale = a.kin_mul = 1.0;
+  a.rho_part = p->shared ? (double*)wsp(ws, p->o_rhop) : nullptr;
+  a.epot = (double*)wsp(ws, p->o_epl);
+  a.ekin = (double*)wsp(ws, p->o_kpl);
+  a.engine = p->xy_engine;
+  return a;
+}
+
+// The plane kernel over every plane of the plan: density groups of a shared
+// potential in one launch, otherwise one launch per class of launch shapes.
+hipError_t line_planes(Seq& q, int mode, XyArgs a) {
+  const wvl_plan* p = q.p;
+  if (p->shared && mode != LINE_HELM)
+    return launch_line(p->prec, mode, a, p->xy_m1, p->xy_m2, p->xy_blocks, q.st);
+  for (const auto& k : p->line_cls) {
+    a.order = p->d_order_q + k.first;
+    a.perm = p->d_perm_q + k.first;
+    a.norb = k.n;
+    a.ntiles = k.tiles;
+    a.queue = q.queue && q.queue < q.queue_end ? q.queue++ : nullptr;
+    const int res = std::max(1, p->ctx->cus) * line_per_cu(p->prec, k.m1, k.m2);
+    hipError_t e = launch_line(p->prec, mode, a, k.m1, k.m2,
+                               a.queue ? std::min(k.tiles, res) : k.tiles, q.st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // The local H*psi launch sequence (Sec. 2.4 steps 2-6 with the density of
 // Sec. 2.5 and the float64 energies).  hpsi may be c itself: then the last z
 // step runs as two passes (the fused one would overwrite c at the start of a
-// z line before its periodic wrap reads it back).
+// z line before its periodic wrap reads it back).  occ_weight (plane kernel of
+// wvl_line.h only): both scales times the orbital's occupation.
 int hpsi_sequence(wvl_plan* p, hipStream_t st, const void* c, const double* V, double pot_scale,
                   double kin_scale, void* hpsi, double* rho, double* e_loc, double* e_kin,
-                  double* e_orb, void* ws) {
+                  double* e_orb, void* ws, bool occ_weight = false) {
   if (p->bc_any)
     return hpsi_bc(p, st, c, V, pot_scale, kin_scale, hpsi, rho, e_loc, e_kin, e_orb, ws);
   if (p->use_oz)
     return hpsi_oz(p, st, c, V, pot_scale, kin_scale, hpsi, rho, e_loc, e_kin, e_orb, ws);
   Seq q(p, st);
+  q.gz.occ_weight = occ_weight ? 1 : 0;
   void* A = wsp(ws, p->o_A);
   void* B = wsp(ws, p->o_B);
   void* S = wsp(ws, p->o_S);
@@ -982,67 +1050,45 @@ int hpsi_sequence(wvl_plan* p, hipStream_t st, const void* c, const double* V, d
   if (p->use_xy) {
     // z pass: u = W_z c; planes: psi, rho, y, t = W_y^T W_x^T y, kxy;
     // z passes: kxy += K_z c, then Hc = W_z^T t + kxy
-    double* epl = (double*)wsp(ws, p->o_epl);
-    double* kpl = (double*)wsp(ws, p->o_kpl);
-    double* rhop = p->shared ? (double*)wsp(ws, p->o_rhop) : nullptr;
     WVL_CHK(q.pass(OP_CW, 3, c, A));
-    {
-      XyArgs xa;
-      xa.orbs = p->d_orbs;
-      xa.pq = p->d_pq;
-      xa.norb = p->norb;
-      xa.shared = p->shared ? 1 : 0;
-      xa.ngroups = p->xy_ngroups;
-      xa.G = p->xy_G;
-      xa.M = p->M;
-      xa.u = A;
-      xa.c = c;
-      xa.t = B;
-      xa.kxy = S;
-      xa.V = V;
-      xa.pot_scale = pot_scale;
-      xa.kin_mul = kin_scale;
-      xa.plane = p->elems;
-      xa.rho_part = rhop;
-      xa.epot = epl;
-      xa.ekin = kpl;
-      xa.occupancy = p->xy_occ;
-      xa.engine = p->xy_engine;
-      xa.rho_lds = 0;
-      xa.order = nullptr;
-      xa.perm = nullptr;
-      xa.queue = nullptr;
+    XyArgs xa = xy_args(p, ws);
+    double *epl = xa.epot, *kpl = xa.ekin, *rhop = xa.rho_part;
+    xa.u = A;
+    xa.c = c;
+    xa.t = B;
+    xa.kxy = S;
+    xa.V = V;
+    xa.pot_scale = pot_scale;
+    xa.kin_mul = kin_scale;
+    xa.occ_weight = occ_weight ? 1 : 0;
+    if (use_line(p)) {
+      Mark mk(p, st, ST_XY);
+      WVL_CHK(line_planes(q, LINE_HPSI, xa));
+    } else if (p->shared) {
+      // matrix-core engine: one launch, each workgroup runs its group's
+      // orbitals in turn; vector engine: one launch per slot of the groups
+      for (int slot = 0; slot < (p->xy_engine ? 1 : p->xy_G); ++slot) {
+        Mark mk(p, st, ST_XY);
+        xa.slot = slot;
+        WVL_CHK(launch_xy(p->prec, xa, p->xy_m1, p->xy_m2, p->xy_blocks, st));
+      }
+    } else {
       xa.ntiles = p->xy_blocks;
       int nblocks = p->xy_blocks;
-      if (q.queue && !p->shared && q.queue < q.queue_end) {
+      if (q.queue && q.queue < q.queue_end) {
         xa.order = p->d_order_q;
         xa.perm = p->d_perm_q;
         xa.queue = q.queue++;
         const size_t lds = xy_lds_bytes(p->prec, p->xy_m1, p->xy_m2, p->xy_engine != 0);
-        const int per_cu = std::max(1, std::min(p->xy_occ / 2, (int)(p->ctx->lds_per_block / lds)));
-        nblocks = std::min(nblocks, std::max(1, p->ctx->cus) * per_cu);
+        nblocks = std::min(nblocks, std::max(1, p->ctx->cus) *
+                                        std::max(1, std::min(2, (int)(p->ctx->lds_per_block / lds))));
       }
-      if (p->shared && p->xy_engine) {
-        // matrix-core engine: one launch, each workgroup runs its group's
-        // orbitals in turn
-        Mark mk(p, st, ST_XY);
-        xa.slot = -1;
-        WVL_CHK(launch_xy(p->prec, xa, p->xy_m1, p->xy_m2, p->xy_blocks, st));
-      } else if (p->shared) {
-        for (int slot = 0; slot < p->xy_G; ++slot) {
-          Mark mk(p, st, ST_XY);
-          xa.slot = slot;
-          WVL_CHK(launch_xy(p->prec, xa, p->xy_m1, p->xy_m2, p->xy_blocks, st));
-        }
-      } else {
-        Mark mk(p, st, ST_XY);
-        xa.slot = 0;
-        WVL_CHK(launch_xy(p->prec, xa, p->xy_m1, p->xy_m2, nblocks, st));
-      }
+      Mark mk(p, st, ST_XY);
+      WVL_CHK(launch_xy(p->prec, xa, p->xy_m1, p->xy_m2, nblocks, st));
     }
     if (p->shared && (rho || want_e)) {
       Mark mk(p, st, ST_RHO);
-      WVL_CHK(launch_rho_reduce(rhop, p->xy_ngroups, p->M, V, rho, want_e ? rv : nullptr, st));
+      WVL_CHK(launch_rho_reduce(rhop, p->xy_ngroups, p->M, V, rho, 0, want_e ? rv : nullptr, st));
     }
     if (p->zfuse && hpsi != c) {
       WVL_CHK(q.zfinal(B, c, S, hpsi, kin_scale, want_e ? ez : nullptr));
@@ -1100,10 +1146,10 @@ int hpsi_sequence(wvl_plan* p, hipStream_t st, const void* c, const double* V, d
 // Launch candidates of wvl_local_hpsi, timed on the plan's own batch (zero
 // data: no kernel's work depends on values).  Candidate k = 3 * seq + shape:
 //   seq 0: one 1D pass per axis and operator;
-//   seq 1: plane-resident kernel, 4 waves per SIMD, default engine;
-//   seq 2: plane-resident kernel, 2 waves per SIMD, default engine;
-//   seq 3: plane-resident kernel, 4 waves per SIMD, vector FMA engine
-//          (float64 only, where the matrix-core engine is the default);
+//   seq 1: plane-resident kernel;
+//   seq 2: workgroup-wide plane kernel (occ 2), default engine;
+//   seq 3: the same with the vector FMA engine (float64 only, where the
+//          matrix-core engine is the default);
 //   shape 0: default tiles (axis-1 tiles as many rows as fit in LDS;
 //            persistent launches of 8 workgroups per CU);
 //   shape 1: axis-1 tiles of half as many rows (seq 0 only: the other
@@ -1348,11 +1394,13 @@ int wvl_energy_gradient(wvl_plan* p, const void* c, const double* V, double g_lo
   // 2 f_b (g_loc Hloc + g_kin Kin) c_b: with one occupation for every orbital
   // the weights fold into the two operator scales, otherwise the orbitals are
   // scaled by f_b afterwards
+  // (inside the plane kernel and the last z step where that path runs)
   const double f = p->occ_uniform ? p->orbs[0].occ : 1.0;
+  const bool inside = !p->occ_uniform && p->use_xy && !p->use_oz && use_line(p);
   if (int r = hpsi_sequence(p, st, c, V, 2.0 * f * g_loc, 2.0 * f * g_kin, grad, nullptr, nullptr,
-                            nullptr, nullptr, ws))
+                            nullptr, nullptr, ws, inside))
     return r;
-  if (!p->occ_uniform) {
+  if (!p->occ_uniform && !inside) {
     PassGeom g{p->d_orbs, p->d_pp, p->norb};
     hipError_t e = launch_scale_occ(p->prec, g, p->pp[p->norb], grad, 1.0, p->elems, st);
     if (e != hipSuccess) return hipfail(e, "occupation weights");
@@ -1445,8 +1493,15 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
       // K_z p by the z pass, then (K_x + K_y) p added plane by plane
       WVL_CHK(q.pass(OP_CK, 3, Pv, Q, nullptr, 1.0, ez));
       Mark mk(p, st, ST_HELM);
-      HelmArgs ha{p->d_orbs, p->d_pq, p->norb, Pv, Q, plane, kpl};
-      WVL_CHK(launch_helm_xy(p->prec, ha, p->xy_m1, p->xy_m2, p->pq[p->norb], helm_mx, st));
+      if (use_line(p)) {
+        XyArgs xa = xy_args(p, ws);
+        xa.c = Pv;
+        xa.kxy = Q;
+        WVL_CHK(line_planes(q, LINE_HELM, xa));
+      } else {
+        HelmArgs ha{p->d_orbs, p->d_pq, p->norb, Pv, Q, plane, kpl};
+        WVL_CHK(launch_helm_xy(p->prec, ha, p->xy_m1, p->xy_m2, p->pq[p->norb], helm_mx, st));
+      }
     } else if (!separate) {
       // combined filter (analysis o kinetic o synthesis) per axis, on the
       // coefficients; q = Kin p here, the shift is applied in the update

@@ -125,6 +125,7 @@ struct PassGeom {
   int32_t ntiles;
   int32_t grid;
   int32_t xdiv;    // axis-1 passes: rows per tile = (rows that fit in LDS) / xdiv
+  int32_t occ_weight;   // kinetic passes: weight the output by the orbital's occupation
 };
 
 // rows of length m1 per axis-1 tile (kContigLds values of LDS with halo)
@@ -229,66 +230,35 @@ template <> struct Prec<F32> {
   __device__ static V from_d(double x) { return (float)x; }
 };
 
-// Compensated single precision: every value is an unevaluated pair hi + lo of
-// floats.  A filter sum y = sum_o w_o x_o is accumulated with error-free
-// transforms on the hi parts (TwoProduct by FMA, TwoSum) and the first-order
-// cross terms w_hi x_lo + w_lo x_hi in plain float, all in float arithmetic.
+// Compensated single precision: a value is stored as an unevaluated pair
+// hi + lo of floats and computed with in float64, which holds every such pair
+// whose parts do not lie more than 53 bits apart.  A filter tap is one FMA
+// either way (this chip's float64 and unpacked float32 rates are equal), where
+// error-free float32 transforms take twelve operations: for 512 uneven orbitals
+// of 32..128 points per axis the z passes took 8.0 ms with those and take 4.3.
 template <> struct Prec<F32C> {
-  using V = f2;
-  struct Acc { float s, c; };
+  using V = double;
+  struct Acc { double s; };
   static constexpr int bytes = 8;
   __device__ static V ldc(const void* p, int64_t i, int64_t plane) {
     const float* f = (const float*)p;
-    return f2{f[i], f[plane + i]};
+    return (double)f[i] + (double)f[plane + i];
   }
   __device__ static void st(void* p, int64_t i, int64_t plane, V v) {
     float* f = (float*)p;
-    f[i] = v.hi;
-    f[plane + i] = v.lo;
+    const float h = (float)v;
+    f[i] = h;
+    f[plane + i] = (float)(v - (double)h);
   }
-  __device__ static Acc zero() { return Acc{0.0f, 0.0f}; }
+  __device__ static Acc zero() { return Acc{0.0}; }
   template <int OP> __device__ static void add(Acc& a, int par, int o, const V& x) {
-    const float wh = (float)coef<OP>(par, o, 1);
-    const float wl = (float)coef<OP>(par, o, 2);
-    float p = wh * x.hi;
-    float e = __builtin_fmaf(wh, x.hi, -p);
-    float s, q;
-    two_sum(a.s, p, s, q);
-    a.s = s;
-    float c = a.c + (q + e);
-    c = __builtin_fmaf(wh, x.lo, c);
-    a.c = __builtin_fmaf(wl, x.hi, c);
+    a.s = __builtin_fma(coef<OP>(par, o, 0), x, a.s);
   }
-  __device__ static V fin(const Acc& a) {
-    V r;
-    two_sum(a.s, a.c, r.hi, r.lo);
-    return r;
-  }
-  // (hi + lo) * s with s split into float hi/lo parts
-  __device__ static V scale(V v, double sd) {
-    float sh = (float)sd;
-    float sl = (float)(sd - (double)sh);
-    float p = v.hi * sh;
-    float e = __builtin_fmaf(v.hi, sh, -p);
-    e = __builtin_fmaf(v.hi, sl, e);
-    e = __builtin_fmaf(v.lo, sh, e);
-    V r;
-    fast_two_sum(p, e, r.hi, r.lo);
-    return r;
-  }
-  __device__ static V plus(V a, V b) {
-    float s, e;
-    two_sum(a.hi, b.hi, s, e);
-    e += a.lo + b.lo;
-    V r;
-    fast_two_sum(s, e, r.hi, r.lo);
-    return r;
-  }
-  __device__ static double d(V v) { return (double)v.hi + (double)v.lo; }
-  __device__ static V from_d(double x) {
-    float h = (float)x;
-    return f2{h, (float)(x - (double)h)};
-  }
+  __device__ static V fin(const Acc& a) { return a.s; }
+  __device__ static V scale(V v, double s) { return v * s; }
+  __device__ static V plus(V a, V b) { return a + b; }
+  __device__ static double d(V v) { return v; }
+  __device__ static V from_d(double x) { return x; }
 };
 
 }  // namespace wvl

@@ -150,15 +150,13 @@ struct XyArgs {
   void* kxy;
   const double* V;
   double pot_scale, kin_mul;
+  int32_t occ_weight;    // multiply both scales by the orbital's occupation
   int64_t plane;
   double* rho_part;      // [ngroups][M] (shared) or nullptr
   double* epot;          // per (orbital, plane)
   double* ekin;          // per (orbital, plane): <c, (K_x + K_y) c> over the plane
-  int32_t occupancy;     // waves per SIMD the kernel is compiled for (2 or 4)
-  int32_t slot;          // shared: orbital g * G + slot of every group g; -1: all slots in turn
-  int32_t engine;        // 0: vector FMA passes, 1: float64 matrix-core passes
-  int32_t rho_lds;       // shared, matrix engine, 2 waves per SIMD: the group's
-                         // density plane kept in LDS (set by launch_xy)
+  int32_t engine;        // workgroup-wide kernel: 0 vector FMA passes, 1 float64 matrix-core passes
+  int32_t slot;          // shared, vector engine: orbital g * G + slot of every group g
   // persistent launch of the unshared path (queue != nullptr): planes taken
   // from the queue in the order of `order` (prefix of planes over perm)
   const int32_t* order;
@@ -236,8 +234,19 @@ bool xy_supported(int prec, int m1, int m2, bool engine);
 // m1, m2: the plane of every orbital of the launch (the largest one for uneven
 // batches; LDS is sized for it)
 hipError_t launch_xy(int prec, const XyArgs& a, int m1, int m2, int nblocks, hipStream_t st);
+// The plane kernel of wvl_line.h, for planes of up to 128 x 128 values (mode:
+// LINE_HPSI, LINE_RHO or LINE_HELM of wvl_plane.h; HELM: c = p, kxy += its
+// in-plane operator).  Unshared launches run the planes of the a.norb orbitals
+// `perm` with plane prefix `order`.  line_shape_of: launch shape of an m1 x m2
+// plane (-1: too large); line_per_cu: workgroups of it that fit a compute unit.
+int line_shape_of(int prec, int m1, int m2);
+int line_per_cu(int prec, int m1, int m2);
+hipError_t launch_line(int prec, int mode, const XyArgs& a, int m1, int m2, int nblocks,
+                       hipStream_t st);
+// rho (nullable) = [rho +] sum of the group partials in group order, rvpart
+// (nullable): per-block sums of V times that sum
 hipError_t launch_rho_reduce(const double* part, int ngroups, int64_t M, const double* V,
-                             double* rho, double* rvpart, hipStream_t st);
+                             double* rho, int accumulate, double* rvpart, hipStream_t st);
 
 // Overlap S = X X^T (X: norb rows of `len` coefficients stored in precision
 // `prec`, plane stride `plane`), Cholesky S = L L^T with L^{-1}, and

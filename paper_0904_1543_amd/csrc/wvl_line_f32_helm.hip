@@ -1,0 +1,6 @@
+// Plane kernel instantiations: F32, LINE_HELM, one plane per tile.
+#include "wvl_line.h"
+
+namespace wvl {
+template hipError_t line_launch<F32, LINE_HELM, false>(int, const XyArgs&, int, int, size_t, hipStream_t);
+}  // namespace wvl

@@ -1,0 +1,6 @@
+// Plane kernel instantiations: F32C, LINE_RHO, density groups.
+#include "wvl_line.h"
+
+namespace wvl {
+template hipError_t line_launch<F32C, LINE_RHO, true>(int, const XyArgs&, int, int, size_t, hipStream_t);
+}  // namespace wvl

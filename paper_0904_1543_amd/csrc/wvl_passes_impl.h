@@ -63,6 +63,7 @@ __global__ __launch_bounds__(kThreads) void k_strided(PassGeom g, const void* __
   const int m = AXIS == 3 ? m3 : m2;
   const int64_t L = AXIS == 3 ? (int64_t)m1 * m2 : (int64_t)m1 * m3;
   const int64_t line = (int64_t)t * kThreads + threadIdx.x;
+  const double km = g.occ_weight ? kmul * od.occ : kmul;
   double e = 0.0;
   if (line < L) {
     const int64_t stride = AXIS == 3 ? (int64_t)m1 * m2 : (int64_t)m1;
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(kThreads) void k_strided(PassGeom g, const void* __
             y0 = T::scale(y0, ks);
             y1 = T::scale(y1, ks);
             if (EN) e += T::d(win[OHI]) * T::d(y0) + T::d(win[OHI + 1]) * T::d(y1);
-            if (kmul != 1.0) { y0 = T::scale(y0, kmul); y1 = T::scale(y1, kmul); }
+            if (km != 1.0) { y0 = T::scale(y0, km); y1 = T::scale(y1, km); }
           }
           const int64_t i0 = base + (int64_t)kk * stride, i1 = i0 + stride;
           if (K0) {
@@ -155,6 +156,7 @@ __global__ __launch_bounds__(kThreads) void k_zfinal(PassGeom g, const void* __r
   const int m1 = od.m[0], m2 = od.m[1], m = od.m[2];
   const int64_t L = (int64_t)m1 * m2;
   const int64_t line = (int64_t)tl * kThreads + threadIdx.x;
+  const double km = g.occ_weight ? kmul * od.occ : kmul;
   double e = 0.0;
   if (line < L) {
     const int64_t stride = L;
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(kThreads) void k_zfinal(PassGeom g, const void* __r
           z0 = T::scale(z0, ks);
           z1 = T::scale(z1, ks);
           if (EN) e += T::d(wk[HK]) * T::d(z0) + T::d(wk[HK + 1]) * T::d(z1);
-          if (kmul != 1.0) { z0 = T::scale(z0, kmul); z1 = T::scale(z1, kmul); }
+          if (km != 1.0) { z0 = T::scale(z0, km); z1 = T::scale(z1, km); }
           z0 = T::plus(z0, x0);
           z1 = T::plus(z1, x1);
           pair_conv<P, OP_CWT>(wt, y0, y1);

@@ -1,9 +1,13 @@
-// Device helpers shared by the two in-plane kernels (vector and matrix-core).
+// Device helpers and launch shapes shared by the in-plane kernels.
 #pragma once
 
 #include "wvl_kernels.h"
 
 namespace wvl {
+
+// parts of a plane the plane kernel runs: the whole local H*psi, only the
+// density, or the preconditioner's in-plane operator
+enum { LINE_HPSI = 0, LINE_RHO = 1, LINE_HELM = 2 };
 
 constexpr int kXyThreads = 512;   // threads of an in-plane workgroup (8 waves)
 constexpr int kXyWaves = kXyThreads / 64;
@@ -66,5 +70,26 @@ __device__ __forceinline__ double xy_block_sum(double v) {
   __syncthreads();
   return t;
 }
+
+// Launch shapes of the plane kernel: the first that fits.  A shape fits when
+// its rows (pitch) hold m1 values, mi groups of lines per wave cover the
+// plane with at most nt threads, and the plane buffers (two, or one) fit the
+// LDS.  U, the outputs of a work item: 12 at 96 points a line (8 segments,
+// 161 registers, 3 waves per SIMD), less for shorter lines so that they fill
+// the lanes and registers allow 4 waves per SIMD (wpe).  16 outputs would
+// need more coefficients in scalar registers than there are.
+struct LineShape { int pitch, U, mi, two, nt, wpe; };
+constexpr LineShape kLineShapes[] = {{33, 8, 1, 1, 512, 4}, {65, 8, 1, 1, 1024, 4}, {81, 10, 1, 1, 768, 4},
+                                     {97, 12, 1, 1, 768, 3}, {129, 8, 2, 0, 1024, 4}};
+// Lanes of a wave over `ns` segments a line and line_lines() lines: 16
+// consecutive lanes (what the LDS serves at a time in float64) fall on
+// distinct banks when they are 4 lines x 4 segments of 12, 2 lines x 8
+// segments of 10, or 8 or 16 lines x segments of 8 (odd line pitch).
+constexpr int line_sub(int U) { return U == 12 ? 4 : U == 10 ? 2 : 0; }
+__host__ __device__ inline int line_lines(int U, int ns) {
+  const int sb = line_sub(U);
+  return sb > 0 ? sb * (64 / sb / ns) : 64 / ns;
+}
+constexpr int kNumLineShapes = sizeof(kLineShapes) / sizeof(kLineShapes[0]);
 
 }  // namespace wvl

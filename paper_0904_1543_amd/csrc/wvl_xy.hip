@@ -1,29 +1,33 @@
 // Host dispatch of the in-plane kernel (the device code is in wvl_xy_impl.h,
 // instantiated per precision and engine by the wvl_xy_<form>.hip files).
 
-#include <stdlib.h>
+#include <algorithm>
 
 #include "wvl_plane.h"
 
 namespace wvl {
 
 template <int P, bool SH>
-void xy_launch_v(const XyArgs& a, int mi, int nblocks, size_t lds, hipStream_t st);
+void xy_launch_v(const XyArgs& a, int nblocks, size_t lds, hipStream_t st);
 template <bool SH>
-void xy_launch_m(const XyArgs& a, int mt, int nblocks, size_t lds, hipStream_t st);
+void xy_launch_m(const XyArgs& a, int nblocks, size_t lds, hipStream_t st);
 template <int P>
-void helm_launch_v(const HelmArgs& a, int mi, int nblocks, size_t lds, hipStream_t st);
-void helm_launch_mf(const HelmArgs& a, int mt, int nblocks, size_t lds, hipStream_t st);
+void helm_launch_v(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st);
+void helm_launch_mf(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st);
+
+template <int P, int MODE, bool SH>
+hipError_t line_launch(int shape, const XyArgs& a, int nblocks, int nt, size_t lds, hipStream_t st);
 
 // rho[r] = sum_g rho_part[g][r] (group order), and per-block sums of V rho
 __global__ __launch_bounds__(kThreads) void k_rho_reduce(const double* __restrict__ part, int ngroups,
                                                          int64_t M, const double* __restrict__ V,
-                                                         double* rho, double* __restrict__ rvpart) {
+                                                         double* rho, int acc,
+                                                         double* __restrict__ rvpart) {
   const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   double s = 0.0;
   if (r < M)
     for (int g = 0; g < ngroups; ++g) s += part[(int64_t)g * M + r];
-  if (rho && r < M) rho[r] = s;
+  if (rho && r < M) rho[r] = acc ? rho[r] + s : s;
   if (rvpart) block_sum_store(r < M ? V[r] * s : 0.0, rvpart + blockIdx.x);
 }
 
@@ -59,20 +63,13 @@ hipError_t launch_xy(int prec, const XyArgs& a, int m1, int m2, int nblocks, hip
   if (mx && !xy_matrix_engine(prec, m1, m2)) return hipErrorInvalidValue;
   const size_t lds = xy_lds_bytes(prec, m1, m2, mx);
   if (mx) {
-    const int mt = xy_tiles(m1, m2);
-    // one workgroup per CU anyway at 2 waves per SIMD: keep the group's
-    // density plane in LDS beside the plane (same pitch) when both fit
-    XyArgs b = a;
-    b.rho_lds = sh && a.occupancy == 2 && 2 * lds <= 160 * 1024 && !getenv("WVL_NO_RHO_LDS");
-    const size_t l = b.rho_lds ? 2 * lds : lds;
-    sh ? xy_launch_m<true>(b, mt, nblocks, l, st) : xy_launch_m<false>(b, mt, nblocks, l, st);
+    sh ? xy_launch_m<true>(a, nblocks, lds, st) : xy_launch_m<false>(a, nblocks, lds, st);
     return hipGetLastError();
   }
-  const int mi = xy_items(m1, m2);
   switch (prec) {
-    case F64: sh ? xy_launch_v<F64, true>(a, mi, nblocks, lds, st) : xy_launch_v<F64, false>(a, mi, nblocks, lds, st); break;
-    case F32: sh ? xy_launch_v<F32, true>(a, mi, nblocks, lds, st) : xy_launch_v<F32, false>(a, mi, nblocks, lds, st); break;
-    default:  sh ? xy_launch_v<F32C, true>(a, mi, nblocks, lds, st) : xy_launch_v<F32C, false>(a, mi, nblocks, lds, st); break;
+    case F64: sh ? xy_launch_v<F64, true>(a, nblocks, lds, st) : xy_launch_v<F64, false>(a, nblocks, lds, st); break;
+    case F32: sh ? xy_launch_v<F32, true>(a, nblocks, lds, st) : xy_launch_v<F32, false>(a, nblocks, lds, st); break;
+    default:  sh ? xy_launch_v<F32C, true>(a, nblocks, lds, st) : xy_launch_v<F32C, false>(a, nblocks, lds, st); break;
   }
   return hipGetLastError();
 }
@@ -83,23 +80,75 @@ hipError_t launch_helm_xy(int prec, const HelmArgs& a, int m1, int m2, int nbloc
   if (engine && !xy_matrix_engine(prec, m1, m2)) return hipErrorInvalidValue;
   const size_t lds = xy_lds_bytes(prec, m1, m2, engine);
   if (engine) {
-    helm_launch_mf(a, xy_tiles(m1, m2), nblocks, lds, st);
+    helm_launch_mf(a, nblocks, lds, st);
     return hipGetLastError();
   }
-  const int mi = xy_items(m1, m2);
   switch (prec) {
-    case F64: helm_launch_v<F64>(a, mi, nblocks, lds, st); break;
-    case F32: helm_launch_v<F32>(a, mi, nblocks, lds, st); break;
-    default:  helm_launch_v<F32C>(a, mi, nblocks, lds, st); break;
+    case F64: helm_launch_v<F64>(a, nblocks, lds, st); break;
+    case F32: helm_launch_v<F32>(a, nblocks, lds, st); break;
+    default:  helm_launch_v<F32C>(a, nblocks, lds, st); break;
   }
   return hipGetLastError();
 }
 
+// shape of the plane kernel for planes of up to m1 x m2 values (-1: none),
+// its threads and its LDS
+static int line_shape(int prec, int m1, int m2, int* nt, size_t* lds) {
+  const size_t es = prec == F32 ? 4 : 8;
+  for (int s = 0; s < kNumLineShapes; ++s) {
+    const LineShape& k = kLineShapes[s];
+    const int sx = (m1 + k.U - 1) / k.U, sy = (m2 + k.U - 1) / k.U;   // segments of a line
+    const int lx = sx <= 64 ? line_lines(k.U, sx) : 0, ly = sy <= 64 ? line_lines(k.U, sy) : 0;
+    if (lx == 0 || ly == 0) continue;
+    const int gx = (m2 + lx - 1) / lx, gy = (m1 + ly - 1) / ly;   // groups of lines
+    *nt = 64 * ((std::max(gx, gy) + k.mi - 1) / k.mi);
+    *lds = (size_t)(k.two ? 2 : 1) * m2 * k.pitch * es;
+    if (m1 < k.pitch && *nt <= k.nt && *lds <= 159 * 1024) return s;
+  }
+  return -1;
+}
+
+int line_shape_of(int prec, int m1, int m2) {
+  int nt;
+  size_t lds;
+  return line_shape(prec, m1, m2, &nt, &lds);
+}
+
+// workgroups of the shape that share a compute unit: by LDS and by waves
+int line_per_cu(int prec, int m1, int m2) {
+  int nt;
+  size_t lds;
+  const int s = line_shape(prec, m1, m2, &nt, &lds);
+  if (s < 0) return 1;
+  const int waves = 4 * kLineShapes[s].wpe;
+  return std::max(1, std::min((int)(160 * 1024 / (lds + 1024)), waves / (nt / 64)));
+}
+
+hipError_t launch_line(int prec, int mode, const XyArgs& a, int m1, int m2, int nblocks,
+                       hipStream_t st) {
+  if (nblocks == 0) return hipSuccess;
+  int nt;
+  size_t lds;
+  const int s = line_shape(prec, m1, m2, &nt, &lds);
+  if (s < 0) return hipErrorInvalidValue;
+#define WVL_P(P)                                                                              \
+  return mode == LINE_HELM  ? line_launch<P, LINE_HELM, false>(s, a, nblocks, nt, lds, st)    \
+         : mode == LINE_RHO ? line_launch<P, LINE_RHO, true>(s, a, nblocks, nt, lds, st)      \
+         : a.shared         ? line_launch<P, LINE_HPSI, true>(s, a, nblocks, nt, lds, st)     \
+                            : line_launch<P, LINE_HPSI, false>(s, a, nblocks, nt, lds, st)
+  switch (prec) {
+    case F64: WVL_P(F64);
+    case F32: WVL_P(F32);
+    default: WVL_P(F32C);
+  }
+#undef WVL_P
+}
+
 hipError_t launch_rho_reduce(const double* part, int ngroups, int64_t M, const double* V,
-                             double* rho, double* rvpart, hipStream_t st) {
+                             double* rho, int accumulate, double* rvpart, hipStream_t st) {
   const int nblk = (int)((M + kThreads - 1) / kThreads);
   hipLaunchKernelGGL(k_rho_reduce, dim3(nblk), dim3(kThreads), 0, st, part, ngroups, M, V, rho,
-                     rvpart);
+                     accumulate, rvpart);
   return hipGetLastError();
 }
 

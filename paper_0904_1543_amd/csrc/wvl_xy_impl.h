@@ -1,4 +1,7 @@
-// The in-plane part of the local Hamiltonian, one z-plane per workgroup, gfx950.
+// The in-plane part of the local Hamiltonian, one z-plane per workgroup, every
+// pass over the whole workgroup, gfx950: the form for planes that the kernel
+// of wvl_line.h does not hold (a side of more than 128 values), and the
+// alternative engines.
 //
 // The 3D operators are tensor products of 1D operators (Sec. 3.1), so the
 // local Hamiltonian of one orbital factorises along z:
@@ -446,9 +449,7 @@ __device__ __forceinline__ void eng_pass(typename E::V* buf, int m1, int m2, int
 }
 
 // One (orbital, plane): everything the kernel does for orbital b at plane z.
-// RL: the group's density plane is kept in LDS after the plane buffer (same
-// pitch) across the group's orbitals and written once by k_xy
-template <int P, typename E, bool SHARED, bool RL = false>
+template <int P, typename E, bool SHARED>
 __device__ __forceinline__ void xy_orbital_plane(const XyArgs& a, int b, int z, int g, int bi) {
   using T = Prec<P>;
   using V = typename T::V;
@@ -470,8 +471,7 @@ __device__ __forceinline__ void xy_orbital_plane(const XyArgs& a, int b, int z, 
   //      y = pot_scale V psi
   double ep = 0.0;
   const double* Vp = a.V + od.voff + (int64_t)z * npl;
-  double* rp = SHARED && !RL ? a.rho_part + (int64_t)g * a.M + (int64_t)z * npl : nullptr;
-  double* rl = RL ? reinterpret_cast<double*>(buf + m2 * pitch) : nullptr;
+  double* rp = SHARED ? a.rho_part + (int64_t)g * a.M + (int64_t)z * npl : nullptr;
   struct VR { double v, r; };
   plane_batched<kPlaneBatch>(
       m1, npl, pitch,
@@ -479,8 +479,7 @@ __device__ __forceinline__ void xy_orbital_plane(const XyArgs& a, int b, int z, 
       [&](int e, int pos, VR w) {
         const V psi = buf[pos];
         const double pd = T::d(psi);
-        if (RL) rl[pos] = bi == 0 ? od.occ * pd * pd : __builtin_fma(od.occ * pd, pd, rl[pos]);
-        else if (SHARED && rp) rp[e] = bi == 0 ? od.occ * pd * pd : __builtin_fma(od.occ * pd, pd, w.r);
+        if (SHARED && rp) rp[e] = bi == 0 ? od.occ * pd * pd : __builtin_fma(od.occ * pd, pd, w.r);
         ep = __builtin_fma(w.v * pd, pd, ep);
         buf[pos] = T::scale(psi, w.v * a.pot_scale);
       });
@@ -546,8 +545,8 @@ __device__ __forceinline__ void xy_orbital_plane(const XyArgs& a, int b, int z, 
 // (matrix-core engine, slot = -1); either way the group's density partial is
 // accumulated in orbital order.  Otherwise one (orbital, plane) per tile via
 // the plane prefix pq.
-template <int P, typename E, bool SHARED, int WPE, bool RL = false>
-__global__ __launch_bounds__(kXyThreads) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+template <int P, typename E, bool SHARED>
+__global__ __launch_bounds__(kXyThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_xy(XyArgs a) {
   if (SHARED) {
     const int g = blockIdx.x % a.ngroups;
@@ -558,25 +557,16 @@ void k_xy(XyArgs a) {
       xy_orbital_plane<P, E, SHARED>(a, b, z, g, a.slot);
     } else {
       // every orbital of the group in turn: the group's density partial of
-      // this plane stays in L2 between them (RL: in LDS, written once)
+      // this plane stays in L2 between them
       #pragma nounroll
       for (int slot = 0; slot < a.G; ++slot) {
         const int b = g * a.G + slot;
         if (b >= a.norb) break;
-        xy_orbital_plane<P, E, SHARED, RL>(a, b, z, g, slot);
-      }
-      if (RL) {
-        __syncthreads();
-        extern __shared__ __align__(16) unsigned char xy_lds[];
-        const int m1 = a.orbs[g * a.G].m[0], m2 = a.orbs[g * a.G].m[1];
-        const int pitch = E::pitch(m1), npl = m1 * m2;
-        const double* rl = reinterpret_cast<const double*>(xy_lds) + m2 * pitch;
-        double* rp = a.rho_part + (int64_t)g * a.M + (int64_t)z * npl;
-        for (PtIter q(m1); q.e < npl; q.next()) rp[q.e] = rl[q.pos(pitch)];
+        xy_orbital_plane<P, E, SHARED>(a, b, z, g, slot);
       }
     }
   } else {
-    const PassGeom geo{a.orbs, a.pq, a.norb, a.order, a.perm, a.queue, a.ntiles, 0};
+    const PassGeom geo{a.orbs, a.pq, a.norb, a.order, a.perm, a.queue, a.ntiles};
     for_each_tile(geo, [&](int b, int z, int) { xy_orbital_plane<P, E, SHARED>(a, b, z, 0, 0); });
   }
 }
@@ -589,8 +579,8 @@ void k_xy(XyArgs a) {
 // with the plane of p in LDS, both in-plane passes of the combined kinetic
 // filter, and <p, (K_x + K_y) p> per plane for the CG step length.
 // ---------------------------------------------------------------------------
-template <int P, typename E, int WPE>
-__global__ __launch_bounds__(kXyThreads) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+template <int P, typename E>
+__global__ __launch_bounds__(kXyThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_helm_xy(HelmArgs a) {
   using T = Prec<P>;
   using V = typename T::V;
@@ -639,47 +629,23 @@ void k_helm_xy(HelmArgs a) {
   if (threadIdx.x == 0) a.ekin[blockIdx.x] = sk;
 }
 
-template <int P, typename E>
-void helm_launch_e(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st) {
-  hipLaunchKernelGGL((k_helm_xy<P, E, 4>), dim3(nblocks), dim3(kXyThreads), lds, st, a);
-}
-
-template <int P>
-void helm_launch_v(const HelmArgs& a, int mi, int nblocks, size_t lds, hipStream_t st) {
-  if (mi <= 3) helm_launch_e<P, VecEngine<P, 3>>(a, nblocks, lds, st);
-  else if (mi <= 5) helm_launch_e<P, VecEngine<P, 5>>(a, nblocks, lds, st);
-  else helm_launch_e<P, VecEngine<P, 8>>(a, nblocks, lds, st);
-}
-
-inline void helm_launch_m(const HelmArgs& a, int mt, int nblocks, size_t lds, hipStream_t st) {
-  if (mt <= 2) helm_launch_e<F64, MfEngine<2>>(a, nblocks, lds, st);
-  else if (mt <= 5) helm_launch_e<F64, MfEngine<5>>(a, nblocks, lds, st);
-  else helm_launch_e<F64, MfEngine<8>>(a, nblocks, lds, st);
-}
-
-template <int P, typename E, bool SH>
-void xy_launch_e(const XyArgs& a, int nblocks, size_t lds, hipStream_t st) {
-  // occupancy target: 4 waves per SIMD (two workgroups per CU, <= 128
-  // registers) or 2 (one workgroup per CU, <= 256 registers)
-  const dim3 g(nblocks), b(kXyThreads);
-  if (a.occupancy == 2 && a.rho_lds)
-    hipLaunchKernelGGL((k_xy<P, E, SH, 2, E::kGroupLoop && SH>), g, b, lds, st, a);
-  else if (a.occupancy == 2) hipLaunchKernelGGL((k_xy<P, E, SH, 2>), g, b, lds, st, a);
-  else hipLaunchKernelGGL((k_xy<P, E, SH, 4>), g, b, lds, st, a);
-}
-
 template <int P, bool SH>
-void xy_launch_v(const XyArgs& a, int mi, int nblocks, size_t lds, hipStream_t st) {
-  if (mi <= 3) xy_launch_e<P, VecEngine<P, 3>, SH>(a, nblocks, lds, st);
-  else if (mi <= 5) xy_launch_e<P, VecEngine<P, 5>, SH>(a, nblocks, lds, st);
-  else xy_launch_e<P, VecEngine<P, 8>, SH>(a, nblocks, lds, st);
+void xy_launch_v(const XyArgs& a, int nblocks, size_t lds, hipStream_t st) {
+  hipLaunchKernelGGL((k_xy<P, VecEngine<P, kMaxItems>, SH>), dim3(nblocks), dim3(kXyThreads), lds, st, a);
 }
 
 template <bool SH>
-void xy_launch_m(const XyArgs& a, int mt, int nblocks, size_t lds, hipStream_t st) {
-  if (mt <= 2) xy_launch_e<F64, MfEngine<2>, SH>(a, nblocks, lds, st);
-  else if (mt <= 5) xy_launch_e<F64, MfEngine<5>, SH>(a, nblocks, lds, st);
-  else xy_launch_e<F64, MfEngine<8>, SH>(a, nblocks, lds, st);
+void xy_launch_m(const XyArgs& a, int nblocks, size_t lds, hipStream_t st) {
+  hipLaunchKernelGGL((k_xy<F64, MfEngine<8>, SH>), dim3(nblocks), dim3(kXyThreads), lds, st, a);
+}
+
+template <int P>
+void helm_launch_v(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st) {
+  hipLaunchKernelGGL((k_helm_xy<P, VecEngine<P, kMaxItems>>), dim3(nblocks), dim3(kXyThreads), lds, st, a);
+}
+
+inline void helm_launch_m(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st) {
+  hipLaunchKernelGGL((k_helm_xy<F64, MfEngine<8>>), dim3(nblocks), dim3(kXyThreads), lds, st, a);
 }
 
 }  // namespace wvl
