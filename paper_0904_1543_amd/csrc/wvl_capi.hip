@@ -1320,12 +1320,18 @@ int wvl_local_density(wvl_plan* p, const void* c, double* rho, int accumulate, v
                               p->elems_rs, rho, accumulate, nullptr, nullptr, st));
     return WVL_OK;
   }
-  WVL_CHK(q.pass(OP_SYN, 3, c, A));
-  WVL_CHK(q.pass(OP_SYN, 2, A, B));
-  WVL_CHK(q.pass(OP_SYN, 1, B, B));
-  WVL_CHK(q.pass(OP_MF, 3, B, A));
-  WVL_CHK(q.pass(OP_MF, 2, A, B));
-  WVL_CHK(q.pass(OP_MF, 1, B, B));
+  // psi with the combined filter; in-plane passes and the sum over a group's
+  // orbitals in the plane kernel where it fits
+  WVL_CHK(q.pass(OP_CW, 3, c, A));
+  if (use_line(p) && (p->use_xy || p->use_oz)) {
+    XyArgs xa = xy_args(p, ws);
+    xa.u = A;
+    WVL_CHK(line_planes(q, LINE_RHO, xa));
+    WVL_CHK(launch_rho_reduce(xa.rho_part, p->xy_ngroups, p->M, nullptr, rho, accumulate, nullptr, st));
+    return WVL_OK;
+  }
+  WVL_CHK(q.pass(OP_CW, 2, A, B));
+  WVL_CHK(q.pass(OP_CW, 1, B, B));
   WVL_CHK(launch_pot_shared(p->prec, p->d_orbs, p->norb, p->M, B, nullptr, nullptr, 1.0, p->elems,
                             rho, accumulate, nullptr, nullptr, st));
   return WVL_OK;
