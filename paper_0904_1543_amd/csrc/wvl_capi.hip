@@ -1666,12 +1666,15 @@ int wvl_local_hpsi_compressed(wvl_plan* p, const void* psi_c, const double* V, d
   hipStream_t st = (hipStream_t)stream;
   const int64_t L = p->nvc + 7 * p->nvf;
   void* full = wsp(ws, p->o_D);
-  // step 1: unpack onto the whole grid; steps 2-6 in place; step 7: pack
+  // step 1: unpack onto the whole grid; steps 2-6; step 7: pack
   WVL_CHK(launch_decompress(p->prec, p->d_orbs, p->norb, p->M, p->d_map_c, p->d_map_f, p->nvc, L,
                             psi_c, L * p->norb, full, p->elems, st));
-  if (int r = hpsi_sequence(p, st, full, V, pot_scale, kin_scale, full, rho, e_loc, e_kin, e_orb, ws))
+  // (into the first workspace array, which every sequence is done with when its
+  // last step writes the result: not in place, so that step may be the fused one)
+  void* hfull = wsp(ws, p->o_A);
+  if (int r = hpsi_sequence(p, st, full, V, pot_scale, kin_scale, hfull, rho, e_loc, e_kin, e_orb, ws))
     return r;
-  WVL_CHK(launch_compress(p->prec, p->d_orbs, p->norb, p->d_list_c, p->d_list_f, p->nvc, L, full,
+  WVL_CHK(launch_compress(p->prec, p->d_orbs, p->norb, p->d_list_c, p->d_list_f, p->nvc, L, hfull,
                           p->elems, hpsi_c, L * p->norb, st));
   return WVL_OK;
 }
