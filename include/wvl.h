@@ -90,9 +90,12 @@ typedef enum { WVL_F64 = 0, WVL_F32 = 1, WVL_F32C = 2 } wvl_prec;
  * M_a = m_a + 29 along isolated axes).  Such plans need WVL_SHARED_V and a
  * dense uniform batch; they run wvl_local_hpsi, wvl_local_density,
  * wvl_energy_gradient, wvl_precondition (combined-filter form), the overlap
- * and orthonormalisation and the compressed-storage calls, with one 1D pass
- * per axis and operator (no plane kernel, no persistent launches, no tuner);
- * wvl_synthesis, wvl_analysis, wvl_magic_filter and wvl_kinetic are
+ * and orthonormalisation and the compressed-storage calls; planes of at most
+ * 128 real-space points per side (49 cells along an isolated axis) run the
+ * in-plane part in the plane kernel, larger ones one 1D pass per axis and
+ * operator (no persistent launches, no tuner; WVL_Q_VARIANT and
+ * WVL_Q_PRECOND_FORM answer 0); wvl_synthesis, wvl_analysis,
+ * wvl_magic_filter and wvl_kinetic are
  * periodic only (WVL_EUNSUPPORTED). */
 #define WVL_FREE_BC    16u
 #define WVL_SURFACE_BC 32u

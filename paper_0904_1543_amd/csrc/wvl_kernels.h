@@ -144,6 +144,9 @@ struct XyArgs {
   int32_t shared;        // shared potential: orbital groups of G, rho partials
   int32_t ngroups, G;
   int64_t M;             // points of the shared grid
+  int32_t free;          // plane kernel: isolated axes (1: axis 1, 2: axis 2; 0, 2 or 3)
+  int32_t m3_rs;         // ... planes of u and t per orbital, in arrays of plane stride plane_u
+  int64_t plane_u;
   const void* u;
   const void* c;
   void* t;
@@ -239,7 +242,7 @@ hipError_t launch_xy(int prec, const XyArgs& a, int m1, int m2, int nblocks, hip
 // in-plane operator).  Unshared launches run the planes of the a.norb orbitals
 // `perm` with plane prefix `order`.  line_shape_of: launch shape of an m1 x m2
 // plane (-1: too large); line_per_cu: workgroups of it that fit a compute unit.
-int line_shape_of(int prec, int m1, int m2);
+int line_shape_of(int prec, int m1, int m2, int free = 0);
 int line_per_cu(int prec, int m1, int m2);
 hipError_t launch_line(int prec, int mode, const XyArgs& a, int m1, int m2, int nblocks,
                        hipStream_t st);

@@ -121,9 +121,21 @@ template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
 // LDS pointers (32-bit, so that window offsets become instruction offsets)
 template <typename C> using Lds = __attribute__((address_space(3))) C*;
 
-template <int OP> constexpr bool line_tap(int par, int o) {
-  return o >= OpWin<OP>::OLO && o <= OpWin<OP>::OHI && coef<OP>(par, o, 0) != 0.0;
-}
+// which taps WO + 16 .. WO - 128 of an operator are not zero, per output parity
+template <int OP>
+struct LineTap {
+  static constexpr int WO = (OpWin<OP>::OHI + 1) & ~1;    // window starts WO before the outputs
+  static constexpr int NT = 128;
+  bool on[2][NT + 16];
+  constexpr LineTap() : on() {
+    for (int p = 0; p < 2; ++p)
+      for (int i = 0; i < NT + 16; ++i) {
+        const int o = WO + i - NT;
+        on[p][i] = o >= OpWin<OP>::OLO && o <= OpWin<OP>::OHI && coef<OP>(p, o, 0) != 0.0;
+      }
+  }
+};
+template <int OP> constexpr LineTap<OP> kLineTap = LineTap<OP>();
 
 // Filter coefficients in the order line_conv takes them up: four per input
 // pair, by one scalar load.  As literals they take two scalar moves each, a
@@ -132,7 +144,7 @@ template <int OP> constexpr bool line_tap(int par, int o) {
 template <int OP, typename C>
 struct LineCoef {
   static constexpr int OLO = OpWin<OP>::OLO, OHI = OpWin<OP>::OHI;
-  static constexpr int WO = (OHI + 1) & ~1;            // window starts WO before the outputs
+  static constexpr int WO = LineTap<OP>::WO, NT = LineTap<OP>::NT;
   static constexpr int NC = (WO - OLO + 3) / 2;        // groups that hold taps
   C v[NC][4];
   static constexpr C at(int p, int o) { return (C)coef<OP>(p, o, sizeof(C) == 4 ? 1 : 0); }
@@ -158,8 +170,11 @@ __device__ __forceinline__ float line_fma(float a, float b, float c) { return __
 // the others have been loaded for earlier pairs.  mc and the start of the
 // window are even: a pair never straddles the periodic wrap.
 // PRIO: the wave's issue priority, one lower in the second half.
-template <int OP, int U, int ST, int PRIO, typename C>
-__device__ __forceinline__ void line_conv(Lds<C> line, int mc, int k0, C (&acc)[U]) {
+// FREE: an isolated line of mc inputs, output k at input position k + d (d
+// even), zero outside: pairs outside read zeros at `zero` (and zero + ST);
+// the value after a line of odd length is zero in LDS.
+template <int OP, int U, int ST, int PRIO, bool FREE, typename C>
+__device__ __forceinline__ void line_conv(Lds<C> line, int mc, int d, int k0, Lds<C> zero, C (&acc)[U]) {
   using K = LineCoef<OP, C>;
   constexpr int OLO = K::OLO, WO = K::WO;
   constexpr int NP = (WO + U - OLO + 1) / 2;      // pairs
@@ -187,20 +202,28 @@ __device__ __forceinline__ void line_conv(Lds<C> line, int mc, int k0, C (&acc)[
         read(std::integral_constant<int, g + 1>{});
         coefs(std::integral_constant<int, g + 1>{});
       }
-      static_for<U>([&](auto u) {
-        constexpr int o = u + WO - 2 * g, h = u / 2;     // tap, and the pairs since its group
-        if constexpr (line_tap<OP>(u & 1, o))
-          acc[u] = line_fma(cf[g - h][u & 1 ? 3 : 0], x0[g % 2], acc[u]);
-      });
-      static_for<U>([&](auto u) {
-        constexpr int o = u + WO - 2 * g - 1, h = u / 2;
-        if constexpr (line_tap<OP>(u & 1, o))
-          acc[u] = line_fma(cf[g - h][u & 1 ? 1 : 2], x1[g % 2], acc[u]);
-      });
+      // output u takes the tap WO - 2 g + u (one less for the second input),
+      // whose group came u / 2 pairs ago
+      #pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (kLineTap<OP>.on[u & 1][u + K::NT - 2 * g])
+          acc[u] = line_fma(cf[g - u / 2][u & 1 ? 3 : 0], x0[g % 2], acc[u]);
+      #pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (kLineTap<OP>.on[u & 1][u + K::NT - 2 * g - 1])
+          acc[u] = line_fma(cf[g - u / 2][u & 1 ? 1 : 2], x1[g % 2], acc[u]);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
-  if (mc >= 2 * NP) {
+  if constexpr (FREE) {
+    const int s0 = k0 + d - WO;
+    const Lds<C> A = line + s0 * ST;
+    run([&](auto g) {
+      const Lds<C> p = (unsigned)(s0 + 2 * g) < (unsigned)mc ? A + 2 * g * ST : zero;
+      x0[g % 2] = p[0];
+      x1[g % 2] = p[ST];
+    });
+  } else if (mc >= 2 * NP) {
     // at most one wrap: two bases, the pair index decides
     const int s0 = k0 < WO ? k0 - WO + mc : k0 - WO;
     const Lds<C> A = line + s0 * ST;
@@ -237,6 +260,12 @@ __device__ __forceinline__ void line_conv(Lds<C> line, int mc, int k0, C (&acc)[
 //   rows:     A: W_x^T, t out;  B: + K_x c, kxy out;  then the next plane's rows
 // Two barriers a plane.  Planes too large for two buffers use one, with c
 // after t (four barriers).
+//
+// Isolated axes (FREE: 1 axis 1, 2 axis 2; Sec. 3.1): lines of m coefficients
+// become m + 29 real-space points and back, so psi fills M1 x M2 = (m1 + 29) x
+// (m2 + 29) points of the plane buffer, whose two rows after the last one stay
+// zero (as does the value after each row).  u and t then have M3 planes and c m3,
+// so K c is a launch of its own (HELM).
 // ---------------------------------------------------------------------------
 typedef const __attribute__((address_space(4))) OrbDev* OrbConst;
 
@@ -257,18 +286,22 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <int P, int PITCH, int U, int MI, bool TWO, int MODE, bool SHARED>
+template <int P, int PITCH, int U, int MI, bool TWO, int MODE, bool SHARED, int FREE>
 struct LineKernel {
   using IO = LineIO<P>;
   using C = typename IO::C;
   using Raw = typename IO::Raw;
+  // H*psi with K c beside u in the second buffer, or after t in the only one
+  static constexpr bool KC = MODE == LINE_HPSI && TWO && !FREE, KC1 = MODE == LINE_HPSI && !TWO && !FREE;
+  static constexpr bool UT = MODE == LINE_HPSI && !KC1;   // the next u is loaded before t goes out
   static constexpr int NPF = U / 2;        // pairs of a group of rows per lane at most
   static constexpr int NW = 16;            // waves at most
 
   const XyArgs& a;
   Lds<C> A, B;
   Lds<double> red;
-  int m1, m2, nw;
+  Lds<C> zero;
+  int m1, m2, M1, M2, nw;
   // this lane's place in a group of rows (x) and of columns (y): line within
   // the group and first output; lines per group; this wave
   int xl, xk, yl, yk, rw, cw, w;
@@ -276,10 +309,18 @@ struct LineKernel {
 
   __device__ __forceinline__ LineKernel(const XyArgs& a_, Lds<C> lds, Lds<double> r, OrbConst od)
       : a(a_), A(lds), red(r), m1(od->m[0]), m2(od->m[1]), nw(blockDim.x >> 6) {
-    B = TWO ? lds + m2 * PITCH : lds;
+    M1 = m1 + line_extra(MODE, FREE & 1);
+    M2 = m2 + line_extra(MODE, FREE & 2);
+    zero = lds + M2 * PITCH;
+    B = TWO && !FREE ? lds + m2 * PITCH : lds;
+    if (FREE) {
+      for (int i = threadIdx.x; i < 2 * PITCH; i += blockDim.x) zero[i] = C(0);
+      for (int i = threadIdx.x; i < M2; i += blockDim.x) lds[i * PITCH + M1] = C(0);   // M1 < PITCH
+      __syncthreads();
+    }
     w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int nsx = (m1 + U - 1) / U, nsy = (m2 + U - 1) / U;
+    const int nsx = (M1 + U - 1) / U, nsy = (M2 + U - 1) / U;
     rw = line_lines(U, nsx);
     cw = line_lines(U, nsy);
     constexpr int SB = line_sub(U);
@@ -316,7 +357,7 @@ struct LineKernel {
   // (0: none).
   template <int AX> __device__ __forceinline__ int first(int i) const { return (w + i * nw) * (AX == 1 ? rw : cw); }
   template <int AX> __device__ __forceinline__ int count(int i) const {
-    return max(0, min(AX == 1 ? rw : cw, (AX == 1 ? m2 : m1) - first<AX>(i)));
+    return max(0, min(AX == 1 ? rw : cw, (AX == 1 ? m2 : M1) - first<AX>(i)));
   }
   // This lane's line (or -1) and first output in group i.  Opaque to the
   // optimiser: window offsets and wrap conditions are computed inside each
@@ -338,7 +379,8 @@ struct LineKernel {
   // Pairs of a group of rows: lane l takes pairs l + 64 n, addressed as a
   // uniform base per n and the lane's offset, clamped to the last pair (no
   // branch around a load; !any: one pair for everybody, nothing to load).
-  __device__ __forceinline__ void load(const void* src, int64_t gp, int i, Raw (&r)[NPF], bool any) const {
+  __device__ __forceinline__ void load(const void* src, int64_t plane, int64_t gp, int i, Raw (&r)[NPF],
+                                       bool any) const {
     int t = threadIdx.x & 63;
     asm volatile("" : "+v"(t));      // offsets are not kept across the loop
     const int lim = any ? max(0, (count<1>(i) * m1 >> 1) - 1) : 0;
@@ -346,7 +388,7 @@ struct LineKernel {
     #pragma unroll
     for (int n = 0; n < NPF; ++n) {
       const int s = min(n * 64, lim);
-      r[n] = IO::ld2(IO::at(src, g0 + 2 * s), 2u * min(t, lim - s), a.plane);
+      r[n] = IO::ld2(IO::at(src, g0 + 2 * s), 2u * min(t, lim - s), plane);
     }
   }
   __device__ __forceinline__ void put(Lds<C> buf, int i, const Raw (&r)[NPF]) const {
@@ -362,7 +404,7 @@ struct LineKernel {
         d[lo[n] + 1] = v1;
       }
   }
-  __device__ __forceinline__ void copy_out(Lds<C> buf, int i, void* dst, int64_t gp) const {
+  __device__ __forceinline__ void copy_out(Lds<C> buf, int i, void* dst, int64_t plane, int64_t gp) const {
     int t = threadIdx.x & 63;
     asm volatile("" : "+v"(t));
     const int np = count<1>(i) * m1 >> 1;
@@ -370,7 +412,7 @@ struct LineKernel {
     const int64_t g0 = gp + first<1>(i) * m1;
     #pragma unroll
     for (int n = 0; n < NPF; ++n)
-      if (t < np - n * 64) IO::st2(IO::at(dst, g0 + 128 * n), 2u * t, a.plane, d[lo[n]], d[lo[n] + 1]);
+      if (t < np - n * 64) IO::st2(IO::at(dst, g0 + 128 * n), 2u * t, plane, d[lo[n]], d[lo[n] + 1]);
   }
   // wait for loaded pairs here
   __device__ __forceinline__ static void arrive(Raw (&r)[MI][NPF]) {
@@ -380,6 +422,13 @@ struct LineKernel {
       for (int n = 0; n < NPF; ++n) IO::pin(r[i][n]);
   }
 
+  // lengths along AX of the inputs and outputs of OP
+  template <int OP, int AX> __device__ __forceinline__ int len_in() const {
+    return AX == 1 ? (OP == OP_CWT ? M1 : m1) : (OP == OP_CWT ? M2 : m2);
+  }
+  template <int OP, int AX> __device__ __forceinline__ int len_out() const {
+    return AX == 1 ? (OP == OP_CW ? M1 : m1) : (OP == OP_CW ? M2 : m2);
+  }
   template <int OP, int AX> __device__ __forceinline__ void conv(Lds<C> src, int i, C (&r)[U]) const {
     // idle lanes repeat the group's first line (their results are not used):
     // no branch, so that nothing has to be kept for the lanes around it
@@ -391,14 +440,17 @@ struct LineKernel {
     // (W^T then W then K by rows, W then W^T then K by columns), so that waves
     // behind catch up.
     constexpr int prio = OP == OP_CK ? 1 : (OP == OP_CW) == (AX == 2) ? 3 : 2;
-    if (AX == 1) line_conv<OP, U, 1, prio>(src + line * PITCH, m1, m.k0, r);
-    else line_conv<OP, U, PITCH, prio>(src + line, m2, m.k0, r);
+    constexpr bool fr = (FREE & AX) != 0;
+    constexpr int d = !fr || OP == OP_CK ? 0 : OP == OP_CW ? -14 : 14;
+    const int n = len_in<OP, AX>();
+    if (AX == 1) line_conv<OP, U, 1, prio, fr>(src + line * PITCH, n, d, m.k0, zero, r);
+    else line_conv<OP, U, PITCH, prio, fr>(src + line, n, d, m.k0, zero, r);
   }
-  // f(u, position in the plane buffer, row, column) for this lane's outputs
-  template <int AX, typename F> __device__ __forceinline__ void each(int i, F&& f) const {
+  // f(u, position in the plane buffer, row, column) for this lane's outputs of OP
+  template <int OP, int AX, typename F> __device__ __forceinline__ void each(int i, F&& f) const {
     const Item m = item<AX>(i);
-    if (!m.on) return;
-    const int mc = AX == 1 ? m1 : m2;
+    if (!m.on || (FREE && OP == OP_CK && AX == 2 && m.line >= m1)) return;
+    const int mc = len_out<OP, AX>();
     const int p0 = AX == 1 ? m.line * PITCH + m.k0 : m.k0 * PITCH + m.line;
     constexpr int es = AX == 1 ? 1 : PITCH;
     if (m.k0 + U <= mc) {
@@ -410,16 +462,17 @@ struct LineKernel {
         if (m.k0 + u < mc) f(u, p0 + u * es, AX == 1 ? m.line : m.k0 + u, AX == 1 ? m.k0 + u : m.line);
     }
   }
-  template <int AX> __device__ __forceinline__ void store(Lds<C> dst, int i, const C (&r)[U]) const {
+  template <int OP, int AX>
+  __device__ __forceinline__ void store(Lds<C> dst, int i, const C (&r)[U]) const {
     wave_sync();
-    each<AX>(i, [&](int u, int pos, int, int) { dst[pos] = r[u]; });
+    each<OP, AX>(i, [&](int u, int pos, int, int) { dst[pos] = r[u]; });
     wave_sync();
   }
   // one pass in place
   template <int OP, int AX> __device__ __forceinline__ void pass(Lds<C> buf, int i) const {
     C r[U];
     conv<OP, AX>(buf, i, r);
-    store<AX>(buf, i, r);
+    store<OP, AX>(buf, i, r);
   }
   // r = s K x along AX for group i, and e += <x, r>
   template <int AX>
@@ -427,16 +480,16 @@ struct LineKernel {
     conv<OP_CK, AX>(buf, i, r);
     #pragma unroll
     for (int u = 0; u < U; ++u) r[u] *= s;
-    each<AX>(i, [&](int u, int pos, int, int) { e = __builtin_fma((double)buf[pos], (double)r[u], e); });
+    each<OP_CK, AX>(i, [&](int u, int pos, int, int) { e = __builtin_fma((double)buf[pos], (double)r[u], e); });
   }
   // the potential at the outputs of group i of columns (zero past the plane
   // and for idle lanes)
   __device__ __forceinline__ void load_v(const char* Vp, int i, double (&v)[U]) const {
     const Item m = item<2>(i);
-    const int x = m.on ? m.line : 0, mc = m.on ? m2 : 0;
+    const int x = m.on ? m.line : 0, mc = m.on ? M2 : 0;
     #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const double q = *reinterpret_cast<const double*>(Vp + 8u * (uint32_t)(min(m.k0 + u, m2 - 1) * m1 + x));
+      const double q = *reinterpret_cast<const double*>(Vp + 8u * (uint32_t)(min(m.k0 + u, M2 - 1) * M1 + x));
       v[u] = m.k0 + u < mc ? q : 0.0;
     }
   }
@@ -456,28 +509,32 @@ struct LineKernel {
       red[(2 * par + 1) * NW + w] = ek;
     }
   }
-  __device__ __forceinline__ void write_energies(int64_t slot, int par) const {
+  __device__ __forceinline__ void write_energies(int b, int z, int par) const {
     if (threadIdx.x != 0) return;
+    const int64_t slot = ((const __attribute__((address_space(4))) int32_t*)a.pq)[b] + z;
     double p = 0.0, k = 0.0;
     for (int i = 0; i < nw; ++i) {
       p += red[(2 * par) * NW + i];
       k += red[(2 * par + 1) * NW + i];
     }
-    if (MODE == LINE_HPSI) a.epot[slot] = p;
-    a.ekin[slot] = k;
-  }
-  __device__ __forceinline__ int64_t slot_of(int b, int z) const {
-    return ((const __attribute__((address_space(4))) int32_t*)a.pq)[b] + z;
+    if (MODE == LINE_HPSI) a.epot[FREE ? (int64_t)b * a.m3_rs + z : slot] = p;
+    if (MODE == LINE_HELM || !FREE) a.ekin[slot] = k;
   }
 
   // The planes z of orbitals b0 .. b1 - 1 in turn (one orbital at least).
   __device__ __forceinline__ void planes(int b0, int b1, int z, double (&rho)[MI][U]) const {
     const int64_t zo = (int64_t)z * (m1 * m2);
     const OrbConst orbs = (OrbConst)a.orbs;
+    // u and t of orbital b (isolated axes: m3_rs planes an orbital)
+    auto uoff = [&](int b) {
+      return FREE ? (int64_t)b * a.m3_rs * (m1 * m2) + zo : orbs[b].off + zo;
+    };
+    const int64_t plane_u = FREE && MODE != LINE_HELM ? a.plane_u : a.plane;
     Raw ru[MI][NPF], rc[MI][NPF];
     #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      load(MODE == LINE_HELM ? a.c : a.u, LineOrb(orbs + b0).off + zo, i, MODE == LINE_HELM ? rc[i] : ru[i], true);
+      if (MODE == LINE_HELM) load(a.c, a.plane, orbs[b0].off + zo, i, rc[i], true);
+      else load(a.u, plane_u, uoff(b0), i, ru[i], true);
     }
     if (MODE != LINE_HELM) arrive(ru);
     #pragma nounroll
@@ -485,7 +542,7 @@ struct LineKernel {
       const LineOrb o(orbs + b);
       const int64_t gp = o.off + zo;
       const bool more = b + 1 < b1;
-      const int64_t gn = orbs[more ? b + 1 : b].off + zo;
+      const int64_t gu = uoff(b), gn = uoff(more ? b + 1 : b);
       const double pot_scale = a.occ_weight ? a.pot_scale * o.occ : a.pot_scale;
       const C km = (C)(a.occ_weight ? a.kin_mul * o.occ : a.kin_mul);
       const int par = b & 1;
@@ -499,10 +556,10 @@ struct LineKernel {
         if (MODE != LINE_HELM) {
           put(A, i, ru[i]);
           wave_sync();
-          if (MODE == LINE_HPSI && TWO) load(a.c, gp, i, rc[i], true);
+          if (KC) load(a.c, a.plane, gp, i, rc[i], true);
           pass<OP_CW, 1>(A, i);
         }
-        if (MODE == LINE_HELM || (MODE == LINE_HPSI && TWO)) {
+        if (MODE == LINE_HELM || KC) {
           put(B, i, rc[i]);
           wave_sync();
           kinetic<1>(B, i, (C)o.ks1, kx[i], ek);
@@ -518,7 +575,7 @@ struct LineKernel {
           C r[U];
           double v[U];
           if (MODE == LINE_HPSI)
-            load_v((const char*)(a.V + o.voff + zo), i, v);
+            load_v((const char*)(a.V + o.voff + (int64_t)z * (M1 * M2)), i, v);
           conv<OP_CW, 2>(A, i, r);
           const bool fst = b == b0;
           #pragma unroll
@@ -531,30 +588,30 @@ struct LineKernel {
             }
           }
           if (MODE == LINE_HPSI) {
-            store<2>(A, i, r);
+            store<OP_CW, 2>(A, i, r);
             pass<OP_CWT, 2>(A, i);
           }
         }
-        if (MODE == LINE_HELM || (MODE == LINE_HPSI && TWO)) {
+        if (MODE == LINE_HELM || KC) {
           C r[U];
           kinetic<2>(B, i, (C)o.ks2, r, ek);
-          store<2>(B, i, r);
+          store<OP_CK, 2>(B, i, r);
         }
       }
       // (the next plane's rows are loaded as late as the registers allow)
-      if (MODE == LINE_RHO || (MODE == LINE_HPSI && TWO)) {
+      if (MODE == LINE_RHO || UT) {
         #pragma unroll
-        for (int i = 0; i < MI; ++i) load(a.u, gn, i, ru[i], more);
+        for (int i = 0; i < MI; ++i) load(a.u, plane_u, gn, i, ru[i], more);
       }
-      if (MODE == LINE_HELM || (MODE == LINE_HPSI && TWO)) energies(ep, ek, par);
+      if (MODE == LINE_HELM || UT) energies(ep, ek, par);
       __syncthreads();
       if (MODE == LINE_RHO) continue;
-      if (TWO || MODE == LINE_HELM) write_energies(slot_of(b, z), par);
+      if (MODE == LINE_HELM || UT) write_energies(b, z, par);
       // ---- rows: W_x^T, t out; kxy out
       if (MODE == LINE_HPSI) {
-        if (!TWO) {
+        if (KC1) {
           #pragma unroll
-          for (int i = 0; i < MI; ++i) load(a.c, gp, i, rc[i], true);
+          for (int i = 0; i < MI; ++i) load(a.c, a.plane, gp, i, rc[i], true);
         }
         #pragma unroll
         for (int i = 0; i < MI; ++i)
@@ -562,19 +619,19 @@ struct LineKernel {
         // the pairs in flight arrive before the stores (whose completion their
         // first use would otherwise wait for: memory operations are counted
         // in order)
-        arrive(TWO ? ru : rc);
+        arrive(KC1 ? rc : ru);
       }
       #pragma unroll
       for (int i = 0; i < MI; ++i) {
         if (count<1>(i) == 0) break;
         if (MODE == LINE_HPSI) {
-          copy_out(A, i, a.t, gp);
-          if (TWO) kxy_out(i, kx[i], km, gp);
+          copy_out(A, i, a.t, plane_u, gu);
+          if (KC) kxy_out(i, kx[i], km, gp);
         } else {
-          helm_out(i, kx[i], gp);
+          helm_out(i, kx[i], km, gp);
         }
       }
-      if (!TWO && MODE == LINE_HPSI) {
+      if (KC1) {
         // one buffer: c after t
         #pragma unroll
         for (int i = 0; i < MI; ++i) {
@@ -590,14 +647,14 @@ struct LineKernel {
           if (count<2>(i) == 0) break;
           C r[U];
           kinetic<2>(A, i, (C)o.ks2, r, ek);
-          store<2>(A, i, r);
+          store<OP_CK, 2>(A, i, r);
         }
         energies(ep, ek, par);
         __syncthreads();
-        write_energies(slot_of(b, z), par);
+        write_energies(b, z, par);
         #pragma unroll
         for (int i = 0; i < MI; ++i) {
-          load(a.u, gn, i, ru[i], more);
+          load(a.u, plane_u, gn, i, ru[i], more);
           if (count<1>(i) == 0) continue;
           kxy_out(i, kx[i], km, gp);
         }
@@ -606,15 +663,15 @@ struct LineKernel {
   }
   // kxy = km (K_x c + K_y c), the latter in B
   __device__ __forceinline__ void kxy_out(int i, const C (&kx)[U], C km, int64_t gp) const {
-    each<1>(i, [&](int u, int pos, int, int) { B[pos] = km * (kx[u] + B[pos]); });
+    each<OP_CK, 1>(i, [&](int u, int pos, int, int) { B[pos] = km * (kx[u] + B[pos]); });
     wave_sync();
-    copy_out(B, i, a.kxy, gp);
+    copy_out(B, i, a.kxy, a.plane, gp);
   }
-  // kq += (K_x + K_y) p
-  __device__ __forceinline__ void helm_out(int i, const C (&kx)[U], int64_t gp) const {
+  // kq = km (kq + (K_x + K_y) p)
+  __device__ __forceinline__ void helm_out(int i, const C (&kx)[U], C km, int64_t gp) const {
     Raw q[NPF];
-    load(a.kxy, gp, i, q, true);
-    each<1>(i, [&](int u, int pos, int, int) { B[pos] += kx[u]; });
+    load(a.kxy, a.plane, gp, i, q, true);
+    each<OP_CK, 1>(i, [&](int u, int pos, int, int) { B[pos] += kx[u]; });
     wave_sync();
     const int np = count<1>(i) * m1 >> 1;
     const Lds<C> d = rows(B, i);
@@ -625,7 +682,7 @@ struct LineKernel {
       if (t < np - n * 64) {
         C v0, v1;
         IO::cvt(q[n], v0, v1);
-        IO::st2(IO::at(a.kxy, g0 + 128 * n), 2u * t, a.plane, v0 + d[lo[n]], v1 + d[lo[n] + 1]);
+        IO::st2(IO::at(a.kxy, g0 + 128 * n), 2u * t, a.plane, km * (v0 + d[lo[n]]), km * (v1 + d[lo[n] + 1]));
       }
   }
 };
@@ -633,10 +690,11 @@ struct LineKernel {
 // Grid: shared potential: blockIdx.x = z * ngroups + g, the orbitals of group
 // g in turn (the density of the group's plane stays in registers and is
 // written once); otherwise one (orbital, a.plane) per tile of the prefix pq.
-template <int P, int PITCH, int U, int MI, bool TWO, int MODE, bool SHARED, int NT, int WPE>
+template <int P, int PITCH, int U, int MI, bool TWO, int MODE, bool SHARED, int FREE, int NT, int WPE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void k_line(XyArgs a) {
-  using K = LineKernel<P, PITCH, U, MI, TWO, MODE, SHARED>;
+#ifdef __HIP_DEVICE_COMPILE__   // (the host pass would instantiate all of it for nothing)
+  using K = LineKernel<P, PITCH, U, MI, TWO, MODE, SHARED, FREE>;
   using C = typename K::C;
   extern __shared__ __align__(16) unsigned char line_lds[];
   __shared__ double red[4 * K::NW];
@@ -648,10 +706,10 @@ void k_line(XyArgs a) {
     const int b0 = g * a.G, b1 = min(b0 + a.G, a.norb);
     const K k(a, lds, rd, (OrbConst)a.orbs + b0);
     k.planes(b0, b1, z, rho);
-    double* rp = a.rho_part + (int64_t)g * a.M + (int64_t)z * (k.m1 * k.m2);
+    double* rp = a.rho_part + (int64_t)g * a.M + (int64_t)z * (k.M1 * k.M2);
     #pragma unroll
     for (int i = 0; i < MI; ++i)
-      k.template each<2>(i, [&](int u, int, int y, int x) { rp[y * k.m1 + x] = rho[i][u]; });
+      k.template each<OP_CW, 2>(i, [&](int u, int, int y, int x) { rp[y * k.M1 + x] = rho[i][u]; });
   } else {
     __shared__ int s_tile;
     for (int vt = blockIdx.x;;) {
@@ -670,15 +728,16 @@ void k_line(XyArgs a) {
       if (a.queue == nullptr) break;
     }
   }
+#endif
 }
 
-template <int P, int MODE, bool SH>
+template <int P, int MODE, bool SH, int FREE>
 hipError_t line_launch(int shape, const XyArgs& a, int nblocks, int nt, size_t lds, hipStream_t st) {
   const dim3 g(nblocks), b(nt);
 #define WVL_LINE(S)                                                                              \
   case S:                                                                                        \
     hipLaunchKernelGGL((k_line<P, kLineShapes[S].pitch, kLineShapes[S].U, kLineShapes[S].mi,      \
-                               kLineShapes[S].two != 0, MODE, SH, kLineShapes[S].nt,             \
+                               kLineShapes[S].two != 0, MODE, SH, FREE, kLineShapes[S].nt,       \
                                kLineShapes[S].wpe>), g, b, lds, st, a);                          \
     break;
   switch (shape) {

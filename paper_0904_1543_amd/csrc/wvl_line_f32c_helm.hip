@@ -2,5 +2,5 @@
 #include "wvl_line.h"
 
 namespace wvl {
-template hipError_t line_launch<F32C, LINE_HELM, false>(int, const XyArgs&, int, int, size_t, hipStream_t);
+template hipError_t line_launch<F32C, LINE_HELM, false, 0>(int, const XyArgs&, int, int, size_t, hipStream_t);
 }  // namespace wvl

@@ -8,6 +8,11 @@ namespace wvl {
 // parts of a plane the plane kernel runs: the whole local H*psi, only the
 // density, or the preconditioner's in-plane operator
 enum { LINE_HPSI = 0, LINE_RHO = 1, LINE_HELM = 2 };
+constexpr int kFreeExtra = 29;   // real-space points added along an isolated axis
+// ... in the plane buffer of a launch (K alone stays on the coefficients)
+__host__ __device__ constexpr int line_extra(int mode, int isolated) {
+  return isolated && mode != LINE_HELM ? kFreeExtra : 0;
+}
 
 constexpr int kXyThreads = 512;   // threads of an in-plane workgroup (8 waves)
 constexpr int kXyWaves = kXyThreads / 64;

@@ -15,7 +15,7 @@ template <int P>
 void helm_launch_v(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st);
 void helm_launch_mf(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st);
 
-template <int P, int MODE, bool SH>
+template <int P, int MODE, bool SH, int FREE>
 hipError_t line_launch(int shape, const XyArgs& a, int nblocks, int nt, size_t lds, hipStream_t st);
 
 // rho[r] = sum_g rho_part[g][r] (group order), and per-block sums of V rho
@@ -93,32 +93,34 @@ hipError_t launch_helm_xy(int prec, const HelmArgs& a, int m1, int m2, int nbloc
 
 // shape of the plane kernel for planes of up to m1 x m2 values (-1: none),
 // its threads and its LDS
-static int line_shape(int prec, int m1, int m2, int* nt, size_t* lds) {
+static int line_shape(int prec, int mode, int m1, int m2, int free, int* nt, size_t* lds) {
   const size_t es = prec == F32 ? 4 : 8;
+  const int M1 = m1 + line_extra(mode, free & 1), M2 = m2 + line_extra(mode, free & 2);
   for (int s = 0; s < kNumLineShapes; ++s) {
     const LineShape& k = kLineShapes[s];
-    const int sx = (m1 + k.U - 1) / k.U, sy = (m2 + k.U - 1) / k.U;   // segments of a line
+    const int sx = (M1 + k.U - 1) / k.U, sy = (M2 + k.U - 1) / k.U;   // segments of a line
     const int lx = sx <= 64 ? line_lines(k.U, sx) : 0, ly = sy <= 64 ? line_lines(k.U, sy) : 0;
     if (lx == 0 || ly == 0) continue;
-    const int gx = (m2 + lx - 1) / lx, gy = (m1 + ly - 1) / ly;   // groups of lines
+    const int gx = (m2 + lx - 1) / lx, gy = (M1 + ly - 1) / ly;   // groups of lines
     *nt = 64 * ((std::max(gx, gy) + k.mi - 1) / k.mi);
-    *lds = (size_t)(k.two ? 2 : 1) * m2 * k.pitch * es;
-    if (m1 < k.pitch && *nt <= k.nt && *lds <= 159 * 1024) return s;
+    // (isolated axes: two rows of zeros after the plane)
+    *lds = (size_t)(M2 + (free ? 2 : 0) + (k.two && !free ? m2 : 0)) * k.pitch * es;
+    if (M1 < k.pitch && *nt <= k.nt && *lds <= 159 * 1024) return s;
   }
   return -1;
 }
 
-int line_shape_of(int prec, int m1, int m2) {
+int line_shape_of(int prec, int m1, int m2, int free) {
   int nt;
   size_t lds;
-  return line_shape(prec, m1, m2, &nt, &lds);
+  return line_shape(prec, LINE_HPSI, m1, m2, free, &nt, &lds);
 }
 
 // workgroups of the shape that share a compute unit: by LDS and by waves
 int line_per_cu(int prec, int m1, int m2) {
   int nt;
   size_t lds;
-  const int s = line_shape(prec, m1, m2, &nt, &lds);
+  const int s = line_shape(prec, LINE_HPSI, m1, m2, 0, &nt, &lds);
   if (s < 0) return 1;
   const int waves = 4 * kLineShapes[s].wpe;
   return std::max(1, std::min((int)(160 * 1024 / (lds + 1024)), waves / (nt / 64)));
@@ -129,18 +131,24 @@ hipError_t launch_line(int prec, int mode, const XyArgs& a, int m1, int m2, int 
   if (nblocks == 0) return hipSuccess;
   int nt;
   size_t lds;
-  const int s = line_shape(prec, m1, m2, &nt, &lds);
+  const int s = line_shape(prec, mode, m1, m2, a.free, &nt, &lds);
   if (s < 0) return hipErrorInvalidValue;
-#define WVL_P(P)                                                                              \
-  return mode == LINE_HELM  ? line_launch<P, LINE_HELM, false>(s, a, nblocks, nt, lds, st)    \
-         : mode == LINE_RHO ? line_launch<P, LINE_RHO, true>(s, a, nblocks, nt, lds, st)      \
-         : a.shared         ? line_launch<P, LINE_HPSI, true>(s, a, nblocks, nt, lds, st)     \
-                            : line_launch<P, LINE_HPSI, false>(s, a, nblocks, nt, lds, st)
+#define WVL_F(P, FR)                                                                             \
+  (mode == LINE_HELM  ? line_launch<P, LINE_HELM, false, FR>(s, a, nblocks, nt, lds, st)         \
+   : mode == LINE_RHO ? line_launch<P, LINE_RHO, true, FR>(s, a, nblocks, nt, lds, st)           \
+                      : line_launch<P, LINE_HPSI, true, FR>(s, a, nblocks, nt, lds, st))
+#define WVL_P(P)                                                                                 \
+  return a.free == 3 ? WVL_F(P, 3)                                                               \
+         : a.free == 2 ? WVL_F(P, 2)                                                             \
+         : mode == LINE_HPSI && !a.shared                                                        \
+             ? line_launch<P, LINE_HPSI, false, 0>(s, a, nblocks, nt, lds, st)                   \
+             : WVL_F(P, 0)
   switch (prec) {
     case F64: WVL_P(F64);
     case F32: WVL_P(F32);
     default: WVL_P(F32C);
   }
+#undef WVL_F
 #undef WVL_P
 }
 
