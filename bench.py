@@ -51,7 +51,7 @@ FLOP_POINTWISE = 4           # rho += f psi^2, V psi
 
 VARIANT_NAMES = {0: "pass-by-pass", 1: "plane-resident",
                  2: "plane-resident (float64)",
-                 3: "exact int8 digit products on the matrix cores (plane-resident)"}
+                 3: "plane-resident (float pairs, last z step fused)"}
 NCAND = 15      # tuner candidates: 5 launch sequences x 3 tile shapes
 
 
@@ -250,7 +250,7 @@ def errors_vs_oracle(got, energies, ref):
 PRECOND_ITERS = 5
 PRECOND_FORMS = {0: "combined filter, one pass per axis",
                  1: "z pass + plane-resident in-plane kernel",
-                 2: "z pass + plane-resident in-plane kernel, exact int8 digit products"}
+                 2: "z pass + plane-resident in-plane kernel (float pairs)"}
 
 
 def run_precond(C, dims, steps, warmup, check):
@@ -402,7 +402,7 @@ def run_uneven(steps, warmup):
     tm = (ctypes.c_double * NCAND)()
     lib.wvl_plan_tuning(plan.h, ctypes.byref(v), tm, NCAND)
     pts = int(sum(np.prod(inputs.fine_shape(d)) for d in dims))
-    seqs = ["pass_by_pass", "plane", "plane_workgroup_wide", "plane_workgroup_wide_vector", "exact_products"]
+    seqs = ["pass_by_pass", "plane", "plane_workgroup_wide", "plane_workgroup_wide_vector", "float_pairs"]
     shapes = ["default_tiles", "half_axis1_tiles", "persistent_4_per_cu"]
     names = [f"{a}/{b}" for a in seqs for b in shapes]
     best = plan.query(lib.WVL_Q_TUNE_BEST)

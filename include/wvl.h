@@ -240,11 +240,12 @@ int wvl_energy_gradient(wvl_plan *plan, const void *c, const double *V, double g
  *         kinetic filter and analysis composed, Sec. 2.4 last paragraph and
  *         Sec. 6.1: the fused wavelet + kinetic kernel), with both in-plane
  *         axes applied by one plane-resident kernel when the plane fits it
- *         (periodic plans), else one pass per axis; WVL_F32C plans that the
- *         exact digit-product engine covers (uniform, fine lengths multiples
- *         of 16, equal spacing on all axes; no shared potential needed) run
- *         that form with exact int8 products (WVL_Q_PRECOND_FORM tells which
- *         form a plan takes); WVL_PRECOND_PASSES: the
+ *         (periodic plans), else one pass per axis; uniform WVL_F32C plans
+ *         whose rows are longer than 128 values run that form with exact
+ *         int8 products where those cover them (fine lengths multiples of 16,
+ *         equal spacing on all axes; no shared potential needed;
+ *         WVL_Q_PRECOND_FORM tells which form a plan takes);
+ *         WVL_PRECOND_PASSES: the
  *         combined filter, one pass per axis; WVL_PRECOND_SEPARATE: the
  *         separate 3D synthesis, kinetic (with K_0) and analysis passes of
  *         the paper's GPU design (Sec. 2.4, Sec. 3.4)
@@ -298,25 +299,25 @@ int wvl_plan_sync(wvl_plan *plan, void *stream);
  * 16 x 16).  Planes of up to 128 x 128 run the kernel in which a wave owns
  * lines of the plane; longer, narrow planes the one that gives a pass to the
  * whole workgroup (on the float64 matrix cores for WVL_F64, vector FMA
- * otherwise).  3: WVL_F32C with exact int8 digit products on
- * the matrix cores (every pass of float pairs split into six base-256 digits
- * per plane, the digit products summed exactly in int32, recombined in
- * int64), chosen for WVL_F32C plans with WVL_SHARED_V, periodic boundaries,
+ * otherwise).  3: WVL_F32C plans with WVL_SHARED_V, periodic boundaries,
  * fine lengths that are multiples of 16, planes of at most 36 tiles of
- * 16 x 16 and the same grid spacing along every axis of an orbital.  Without
+ * 16 x 16 and the same grid spacing along every axis of an orbital: the plane
+ * kernel (float64 arithmetic on the pairs) with the last z step fused; for
+ * rows longer than 128 values exact int8 digit products on the matrix cores
+ * (every pass of float pairs split into six base-256 digits per plane, the
+ * digit products summed exactly in int32, recombined in int64).  Without
  * WVL_AUTOTUNE the environment variable WVL_NO_PLANE_KERNEL forces 0,
  * WVL_F32C_VECTOR keeps WVL_F32C off variant 3 and WVL_XY_VECTOR forces 1
  * over 2 (the workgroup-wide kernel with vector FMA); WVL_PLANE_OCCUPANCY=2
  * runs the workgroup-wide kernel in every precision,
- * WVL_EXACT_OCCUPANCY_Z=2 the last z kernel of variant 3 for 2, and
+ * WVL_EXACT_OCCUPANCY_Z=2 the last z kernel of the digit products for 2, and
  * WVL_NO_ZFUSE runs the last z step as two passes instead of one fused
- * launch (same results bit for bit; the fused launch is used for WVL_F64 and
- * WVL_F32).)  With WVL_AUTOTUNE, times_ms[k] (k < ntimes, at most 15
+ * launch (same results bit for bit; the fused launch is used for WVL_F64,
+ * WVL_F32 and variant 3).)  With WVL_AUTOTUNE, times_ms[k] (k < ntimes, at most 15
  * candidates) receives the mean time of candidate k = 3 seq + shape, or -1
  * where it was not available:
  *   seq 0 one pass per axis; 1 the plane kernel; 2 the workgroup-wide plane
- *   kernel; 3 the same with vector FMA (WVL_F64 only); 4 the exact digit
- *   products (variant 3);
+ *   kernel; 3 the same with vector FMA (WVL_F64 only); 4 variant 3;
  *   shape 0 default tiles; 1 axis-1 tiles of half as many rows (seq 0 only);
  *   2 persistent launches of 4 instead of 8 workgroups per CU (WVL_PERSISTENT
  *   plans only).
@@ -336,9 +337,10 @@ int wvl_plan_tuning(const wvl_plan *plan, int32_t *variant, double *times_ms, in
  *                     not when hpsi is c; see wvl_local_hpsi)
  *   WVL_Q_PRECOND_FORM operator of wvl_precondition's default mode: 0 one
  *                     combined-filter pass per axis, 1 z pass + plane-resident
- *                     in-plane kernel, 2 the same with the exact digit
- *                     products (WVL_F32C uniform periodic plans, fine lengths
- *                     multiples of 16, equal spacing on all axes) */
+ *                     in-plane kernel, 2 the same for WVL_F32C uniform
+ *                     periodic plans, fine lengths multiples of 16, equal
+ *                     spacing on all axes (exact digit products for rows
+ *                     longer than 128 values) */
 #define WVL_Q_VARIANT 0
 #define WVL_Q_GROUP 1
 #define WVL_Q_PERSISTENT 2

@@ -116,8 +116,10 @@ struct wvl_plan {
   struct LineClass { int first, n, m1, m2, tiles; };
   std::vector<LineClass> line_cls;
   bool zfuse = true;   // last two z passes of the plane path fused (not for F32C)
-  // exact-product engine of the compensated form (uniform batches with a
-  // shared potential, lengths multiples of 16, isotropic grid spacing)
+  // compensated uniform plans, lengths multiples of 16, isotropic grid spacing
+  // (variant 3 with a shared potential, preconditioner form 2)
+  bool pairs_iso = false;
+  // ... whose rows are too long for the plane kernel: exact-product engine
   bool oz_ok = false, use_oz = false;
   bool oz_pc = false;   // the preconditioner's operator with the exact products (no potential needed)
   int oz_occ_z = 4;   // waves per SIMD of the exact engine's final z kernel
@@ -464,9 +466,7 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
     bool ok = xy_supported(prec, p->xy_m1, p->xy_m2, mx);
     if (getenv("WVL_NO_PLANE_KERNEL") || p->bc_any) ok = false;
     if (const char* o = getenv("WVL_PLANE_OCCUPANCY")) p->xy_occ = atoi(o) == 2 ? 2 : 4;
-    // compensated float32 keeps two windows of hi/lo pairs: fused, it drops
-    // to one wave per SIMD and is slower than the two passes
-    p->zfuse = prec != WVL_F32C && !getenv("WVL_NO_ZFUSE");
+    p->zfuse = prec != WVL_F32C && !getenv("WVL_NO_ZFUSE");   // (float pairs: below)
     p->use_xy = ok;
     p->xy_ok = !p->bc_any && (xy_supported(prec, p->xy_m1, p->xy_m2, mx) ||
                               xy_supported(prec, p->xy_m1, p->xy_m2, false));
@@ -483,7 +483,12 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
       p->xy_blocks = p->pq[norb];
     }
   }
-  // exact-product engine of the compensated form
+  // Variant 3 of the compensated form.  Planes with a shape of the plane kernel
+  // take it, with the last z step fused: float64 arithmetic on the pairs is
+  // faster than their exact digit products on the matrix cores (256 orbitals of
+  // 48^3 cells: H*psi 6.06 ms against 6.61; error against float64 8e-16 against
+  // 3e-10).  The digit products keep the longer rows, where the other choice
+  // is one pass per axis.
   {
     bool ok = prec == WVL_F32C && uniform && !p->bc_any && !getenv("WVL_F32C_VECTOR") &&
               !getenv("WVL_NO_PLANE_KERNEL");
@@ -492,11 +497,14 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
       const double* k = p->orbs[b].kscale;
       ok = k[0] == k[1] && k[1] == k[2];
     }
-    p->oz_pc = ok;
-    ok = ok && p->shared;
-    p->oz_ok = ok;
-    p->use_oz = ok;
-    if (ok) p->variant = 3;
+    p->pairs_iso = ok;
+    const bool line = ok && p->use_xy && line_shape_of(prec, p->orbs[0].m[0], p->orbs[0].m[1]) >= 0;
+    p->oz_pc = ok && !line;
+    p->oz_ok = p->use_oz = p->oz_pc && p->shared;
+    if (ok && p->shared) {
+      p->variant = 3;
+      p->zfuse = line && !getenv("WVL_NO_ZFUSE");
+    }
     if (const char* o = getenv("WVL_EXACT_OCCUPANCY_Z")) p->oz_occ_z = atoi(o) == 2 ? 2 : 4;
     p->pxz.assign(norb + 1, 0);
     for (int b = 0; b < norb; ++b) p->pxz[b + 1] = p->pxz[b] + p->orbs[b].m[1];
@@ -1229,17 +1237,18 @@ int hpsi_sequence(wvl_plan* p, hipStream_t st, const void* c, const double* V, d
 //            sequences have no axis-1 pass);
 //   shape 2: persistent launches of 4 workgroups per CU (persistent plans).
 // Unavailable candidates get -1.  The fastest one is kept.
-struct Cand { bool xy; int occ, engine, xdiv, pmul; bool oz; };
+struct Cand { bool xy; int occ, engine, xdiv, pmul; bool v3; };
 
 void apply_cand(wvl_plan* p, const Cand& c) {
-  p->use_oz = c.oz;
+  p->use_oz = c.v3 && p->oz_ok;
+  if (p->prec == WVL_F32C) p->zfuse = c.v3 && !p->oz_ok && !getenv("WVL_NO_ZFUSE");
   p->use_xy = c.xy;
   p->xy_occ = c.occ;
   p->xy_engine = c.engine;
   p->xdiv = c.xdiv;
   p->pgrid_mul = c.pmul;
   p->pgrid_pass = std::max(1, p->ctx->cus) * c.pmul;
-  p->variant = c.oz ? 3 : c.xy ? 1 + c.engine : 0;
+  p->variant = c.v3 ? 3 : c.xy ? 1 + c.engine : 0;
 }
 
 int autotune(wvl_plan* p) {
@@ -1248,8 +1257,8 @@ int autotune(wvl_plan* p) {
   const bool vec_ok = xy_supported(p->prec, p->xy_m1, p->xy_m2, false) && !getenv("WVL_NO_PLANE_KERNEL");
   const Cand seqs[5] = {{false, 4, 0, 1, 8, false}, {true, 4, mx ? 1 : 0, 1, 8, false},
                         {true, 2, mx ? 1 : 0, 1, 8, false}, {true, 4, 0, 1, 8, false},
-                        {false, 4, 0, 1, 8, true}};
-  const bool seq_ok[5] = {true, plane_ok, plane_ok, mx && vec_ok, p->oz_ok};
+                        {!p->oz_ok, 4, 0, 1, 8, true}};
+  const bool seq_ok[5] = {true, plane_ok, plane_ok, mx && vec_ok, p->pairs_iso && p->shared};
   const size_t es = p->prec == WVL_F32 ? 4 : 8;
   const size_t arr = (size_t)p->elems * (p->prec == WVL_F32C ? 8 : es);
   const size_t vbytes = sizeof(double) * (size_t)(p->shared ? p->Mrs : std::max<int64_t>(p->vlen, 1));
@@ -1268,7 +1277,7 @@ int autotune(wvl_plan* p) {
   if (err == hipSuccess) err = hipMemsetAsync(V, 0, vbytes, st);
   int status = WVL_OK;
   if (err != hipSuccess) status = hipfail(err, "autotune buffers");
-  const Cand keep{p->use_xy, p->xy_occ, p->xy_engine, p->xdiv, p->pgrid_mul, p->use_oz};
+  const Cand keep{p->use_xy, p->xy_occ, p->xy_engine, p->xdiv, p->pgrid_mul, p->variant == 3};
   int best = -1;
   double best_ms = 0.0;
   p->tune_ms.assign(kTuneCands, -1.0);
@@ -1500,11 +1509,12 @@ int wvl_energy_gradient(wvl_plan* p, const void* c, const double* V, double g_lo
 //   0 one combined-filter pass per axis;
 //   1 the plane-resident form: z pass, then both in-plane passes with the
 //     plane of p in LDS (periodic plans whose planes fit the in-plane kernel);
-//   2 the same two launches with the exact digit products (compensated
-//     uniform periodic plans that the engine covers).
+//   2 the same for compensated uniform periodic plans with lengths that are
+//     multiples of 16 and isotropic spacing; with the exact digit products
+//     where the rows are too long for the plane kernel.
 static int precond_form(const wvl_plan* p, uint32_t mode) {
   if ((mode & (WVL_PRECOND_SEPARATE | WVL_PRECOND_PASSES)) || p->bc_any) return 0;
-  if (p->oz_pc) return 2;
+  if (p->pairs_iso) return 2;
   const bool mx = xy_matrix_engine(p->prec, p->xy_m1, p->xy_m2) && !getenv("WVL_XY_VECTOR");
   return p->xy_ok && xy_supported(p->prec, p->xy_m1, p->xy_m2, mx) ? 1 : 0;
 }
@@ -1548,7 +1558,7 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
   const bool separate = (mode & WVL_PRECOND_SEPARATE) != 0;
   const bool helm_mx = xy_matrix_engine(p->prec, p->xy_m1, p->xy_m2) && !getenv("WVL_XY_VECTOR");
   const int form = precond_form(p, mode);
-  const bool exact = form == 2, plane_form = form == 1;
+  const bool exact = form == 2 && p->oz_pc, plane_form = form != 0 && !exact;
   double* kpl = plane_form || exact ? (double*)wsp(ws, p->o_kpl) : nullptr;
   OzHelmArgs oa{};
   if (exact) {

@@ -185,7 +185,8 @@ hipError_t launch_helm_xy(int prec, const HelmArgs& a, int m1, int m2, int nbloc
 // engine: the float64 matrix-core form of the in-plane passes
 bool xy_matrix_engine(int prec, int m1, int m2);
 // Exact-product engine of the compensated form (wvl_oz.hip): uniform batches
-// with a shared potential, fine lengths multiples of 16.  Float pairs: hi
+// with fine lengths that are multiples of 16 whose rows are too long for the
+// plane kernel of wvl_line.h.  Float pairs: hi
 // plane then lo plane, `plane` floats apart.
 struct OzArgs {
   const OrbDev* orbs;
