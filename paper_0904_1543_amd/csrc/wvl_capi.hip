@@ -105,6 +105,7 @@ struct wvl_plan {
   int64_t vlen = 0;      // minimal length of a per-orbital V buffer
   std::vector<OrbDev> orbs;
   std::vector<int32_t> pz, py, px, pp, pq, pc;
+  int zlen = 0;          // outputs per lane of the axis-3 passes
   int nblk = 0;          // 256-point blocks of the shared grid
   // plane-resident path of wvl_local_hpsi
   bool use_xy = false;
@@ -438,11 +439,21 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
   p->pq.assign(norb + 1, 0);
   p->px2.assign(norb + 1, 0);
   p->pc.assign(norb + 1, 0);
+  {
+    int64_t blocks = 0;
+    int mz = 0;
+    for (const OrbDev& d : p->orbs) {
+      blocks += ((int64_t)d.m[0] * d.m[1] + kThreads - 1) / kThreads;
+      mz = std::max(mz, d.m[2]);
+    }
+    p->zlen = z_segment_length(blocks, mz);
+  }
   for (int b = 0; b < norb; ++b) {
     const OrbDev& d = p->orbs[b];
     const int64_t m1 = d.m[0], m2 = d.m[1], m3 = d.m[2];
+    const int64_t nseg = (m3 + p->zlen - 1) / p->zlen;
     const int64_t R = contig_rows((int)m1, 1), R2 = contig_rows((int)m1, 2);
-    p->pz[b + 1] = p->pz[b] + (int32_t)((m1 * m2 + kThreads - 1) / kThreads);
+    p->pz[b + 1] = p->pz[b] + (int32_t)(nseg * ((m1 * m2 + kThreads - 1) / kThreads));
     p->py[b + 1] = p->py[b] + (int32_t)((m1 * m3 + kThreads - 1) / kThreads);
     p->px[b + 1] = p->px[b] + (int32_t)((m2 * m3 + R - 1) / R);
     p->px2[b + 1] = p->px2[b] + (int32_t)((m2 * m3 + R2 - 1) / R2);
@@ -749,6 +760,7 @@ struct Seq {
   int32_t* queue_end = nullptr;
   Seq(wvl_plan* pl, hipStream_t s) : p(pl), st(s) {
     gz = PassGeom{p->d_orbs, p->d_pz, p->norb};
+    gz.zlen = p->zlen;
     gy = PassGeom{p->d_orbs, p->d_py, p->norb};
     gx = PassGeom{p->d_orbs, p->xdiv == 2 ? p->d_px2 : p->d_px, p->norb};
     gx.xdiv = p->xdiv;

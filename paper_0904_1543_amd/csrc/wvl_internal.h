@@ -11,6 +11,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "filters_gen.h"
 
 namespace wvl {
@@ -126,7 +128,25 @@ struct PassGeom {
   int32_t grid;
   int32_t xdiv;    // axis-1 passes: rows per tile = (rows that fit in LDS) / xdiv
   int32_t occ_weight;   // kinetic passes: weight the output by the orbital's occupation
+  int32_t zlen;         // axis-3 passes: outputs of a line per lane (even)
 };
+
+// Outputs per lane of the axis-3 passes of a batch with `tiles` blocks of
+// kThreads whole lines, the longest of m values.  A lane runs down its line one
+// pair after the other, so a small batch waits for a few long chains: it is cut
+// until there are two workgroups per compute unit (what the registers of the
+// last z step let it hold), each lane reading the filter's reach on both sides
+// of its segment again.  One orbital of 16^3 cells: z pass 10 -> 6 us, last z
+// step 25 -> 15; four workgroups per unit cost 8 orbitals of 32^3 cells 7%
+// (117 -> 126 us), segments of 8 at least cost one of 16^3 4%.
+constexpr int kZTiles = 512;
+constexpr int kZMin = 4;
+inline int z_segment_length(int64_t tiles, int m) {
+  if (tiles >= kZTiles) return m;
+  const int n = (int)((kZTiles + tiles - 1) / tiles);      // segments wanted
+  const int len = (m + n - 1) / n;
+  return std::min(m, std::max(kZMin, (len + 1) & ~1));
+}
 
 // rows of length m1 per axis-1 tile (kContigLds values of LDS with halo)
 __host__ __device__ inline int contig_rows(int m1, int xdiv) {

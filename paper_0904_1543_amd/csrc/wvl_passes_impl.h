@@ -46,6 +46,16 @@ __device__ __forceinline__ void pair_conv(const typename Prec<P>::V* win, typena
   y1 = T::fin(a1);
 }
 
+// Line of this lane in tile t of an axis-3 pass and the outputs [k0, k1) it
+// computes: lines in blocks of kThreads, every block once per segment.
+__device__ __forceinline__ int64_t z_segment(int t, int64_t L, int m, int zlen, int& k0, int& k1) {
+  const int blocks = (int)((L + kThreads - 1) / kThreads);
+  const int seg = t / blocks;
+  k0 = seg * zlen;
+  k1 = min(m, k0 + zlen);
+  return (int64_t)(t - seg * blocks) * kThreads + threadIdx.x;
+}
+
 // ---------------------------------------------------------------------------
 // Strided-axis pass (AXIS = 2 or 3)
 // ---------------------------------------------------------------------------
@@ -62,7 +72,13 @@ __global__ __launch_bounds__(kThreads) void k_strided(PassGeom g, const void* __
   const int m1 = od.m[0], m2 = od.m[1], m3 = od.m[2];
   const int m = AXIS == 3 ? m3 : m2;
   const int64_t L = AXIS == 3 ? (int64_t)m1 * m2 : (int64_t)m1 * m3;
-  const int64_t line = (int64_t)t * kThreads + threadIdx.x;
+  int k0l = 0, k1l = m;   // outputs of this lane
+  int64_t line;
+  if (AXIS == 3) {
+    line = z_segment(t, L, m, g.zlen, k0l, k1l);
+  } else {
+    line = (int64_t)t * kThreads + threadIdx.x;
+  }
   const double km = g.occ_weight ? kmul * od.occ : kmul;
   double e = 0.0;
   if (line < L) {
@@ -72,15 +88,16 @@ __global__ __launch_bounds__(kThreads) void k_strided(PassGeom g, const void* __
     const double ks = AXIS == 3 ? od.kscale[2] : od.kscale[1];
     V win[W + 1];
     #pragma unroll
-    for (int i = 0; i < W - 1; ++i) win[i] = T::ldc(in, base + (int64_t)wrapi(i - OHI, m) * stride, plane);
+    for (int i = 0; i < W - 1; ++i)
+      win[i] = T::ldc(in, base + (int64_t)wrapi(k0l + i - OHI, m) * stride, plane);
     // The loads of the next kPf output pairs are in flight while a pair is
     // computed (ring of registers, refilled as it is consumed): a wave keeps
     // 2 kPf input loads (and as many accumulator loads) outstanding.
     V q0[kPf], q1[kPf], a0[kPf], a1[kPf];
     #pragma unroll
     for (int d = 0; d < kPf; ++d) {
-      const int kk = 2 * d;
-      if (kk < m) {
+      const int kk = k0l + 2 * d;
+      if (kk < k1l) {
         q0[d] = T::ldc(in, base + (int64_t)wrapi(kk - OLO, m) * stride, plane);
         q1[d] = T::ldc(in, base + (int64_t)wrapi(kk + 1 - OLO, m) * stride, plane);
         if (K0) {
@@ -89,17 +106,17 @@ __global__ __launch_bounds__(kThreads) void k_strided(PassGeom g, const void* __
         }
       }
     }
-    for (int k = 0; k < m; k += 2 * kPf) {
+    for (int k = k0l; k < k1l; k += 2 * kPf) {
       #pragma unroll
       for (int d = 0; d < kPf; ++d) {
-        const int kk = k + 2 * d;    // m is even: a pair never straddles the end
-        if (kk < m) {
+        const int kk = k + 2 * d;    // ends are even: a pair never straddles one
+        if (kk < k1l) {
           win[W - 1] = q0[d];
           win[W] = q1[d];
           V c0, c1;
           if (K0) { c0 = a0[d]; c1 = a1[d]; }
           const int kn = kk + 2 * kPf;
-          if (kn < m) {
+          if (kn < k1l) {
             q0[d] = T::ldc(in, base + (int64_t)wrapi(kn - OLO, m) * stride, plane);
             q1[d] = T::ldc(in, base + (int64_t)wrapi(kn + 1 - OLO, m) * stride, plane);
             if (K0) {
@@ -155,7 +172,8 @@ __global__ __launch_bounds__(kThreads) void k_zfinal(PassGeom g, const void* __r
   const OrbDev od = g.orbs[b];
   const int m1 = od.m[0], m2 = od.m[1], m = od.m[2];
   const int64_t L = (int64_t)m1 * m2;
-  const int64_t line = (int64_t)tl * kThreads + threadIdx.x;
+  int k0l, k1l;   // outputs of this lane
+  const int64_t line = z_segment(tl, L, m, g.zlen, k0l, k1l);
   const double km = g.occ_weight ? kmul * od.occ : kmul;
   double e = 0.0;
   if (line < L) {
@@ -165,9 +183,9 @@ __global__ __launch_bounds__(kThreads) void k_zfinal(PassGeom g, const void* __r
     auto at = [&](int i) { return base + (int64_t)wrapi(i, m) * stride; };
     V wt[WT + 1], wk[WK + 1];
     #pragma unroll
-    for (int i = 0; i < WT - 1; ++i) wt[i] = T::ldc(t, at(i - HT), plane);
+    for (int i = 0; i < WT - 1; ++i) wt[i] = T::ldc(t, at(k0l + i - HT), plane);
     #pragma unroll
-    for (int i = 0; i < WK - 1; ++i) wk[i] = T::ldc(c, at(i - HK), plane);
+    for (int i = 0; i < WK - 1; ++i) wk[i] = T::ldc(c, at(k0l + i - HK), plane);
     V qt0[kPfZ], qt1[kPfZ], qk0[kPfZ], qk1[kPfZ], a0[kPfZ], a1[kPfZ];
     auto fetch = [&](int d, int kk) {
       qt0[d] = T::ldc(t, at(kk - LT), plane);
@@ -179,18 +197,18 @@ __global__ __launch_bounds__(kThreads) void k_zfinal(PassGeom g, const void* __r
     };
     #pragma unroll
     for (int d = 0; d < kPfZ; ++d)
-      if (2 * d < m) fetch(d, 2 * d);
-    for (int k = 0; k < m; k += 2 * kPfZ) {
+      if (k0l + 2 * d < k1l) fetch(d, k0l + 2 * d);
+    for (int k = k0l; k < k1l; k += 2 * kPfZ) {
       #pragma unroll
       for (int d = 0; d < kPfZ; ++d) {
-        const int kk = k + 2 * d;    // m is even: a pair never straddles the end
-        if (kk < m) {
+        const int kk = k + 2 * d;    // ends are even: a pair never straddles one
+        if (kk < k1l) {
           wt[WT - 1] = qt0[d];
           wt[WT] = qt1[d];
           wk[WK - 1] = qk0[d];
           wk[WK] = qk1[d];
           const V x0 = a0[d], x1 = a1[d];
-          if (kk + 2 * kPfZ < m) fetch(d, kk + 2 * kPfZ);
+          if (kk + 2 * kPfZ < k1l) fetch(d, kk + 2 * kPfZ);
           V z0, z1, y0, y1;
           pair_conv<P, OP_CK>(wk, z0, z1);
           z0 = T::scale(z0, ks);
