@@ -245,8 +245,8 @@ static CgLayout cg_layout(const wvl_plan* p) {
   CgLayout l;
   l.rz = 0;
   l.pp = np;
-  l.rr = 2 * np;
-  l.eps = 3 * np;
+  l.rr = l.pp + std::max(np, align256(sizeof(double) * (size_t)p->pz[p->norb]));
+  l.eps = l.rr + np;
   l.sc = l.eps + align256(sizeof(double) * (size_t)p->norb);
   l.bytes = l.sc + align256(cg_scalar_bytes() * (size_t)p->norb);
   return l;
@@ -1590,6 +1590,17 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
   }
   WVL_HIP(hipMemcpyAsync(eps_d, eps, sizeof(double) * p->norb, hipMemcpyHostToDevice, st));
   WVL_CHK(launch_cg_init(p->prec, gp, nt, g, gt, R, Pv, eps_d, plane, prz, ppp, prr, st));
+  // periodic combined-filter forms: the direction update of the iteration
+  // before runs inside the z pass, between the arrays Pv and D
+  const bool fused = !p->bc_any && !separate && !exact;
+  const int32_t* ppre = p->d_pc;   // tiles of the partials of p.p
+  auto z_pass = [&](int it) {
+    if (it == 0) return q.pass(OP_CK, 3, Pv, Q, nullptr, 1.0, ez);
+    Mark mk(p, st, stage_of(OP_CK, 3));
+    ppre = p->d_pz;
+    std::swap(Pv, D);
+    return launch_cg_z(p->prec, q.gz, p->pz[p->norb], R, D, Pv, Q, eps_d, sc, plane, ez, ppp, st);
+  };
   for (int it = 0; it < iters; ++it) {
     // q = (A Kin S - eps) p, with the kinetic energy partials p.Kin p
     if (p->bc_line && !(mode & WVL_PRECOND_PASSES)) {
@@ -1609,7 +1620,7 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
       WVL_CHK(launch_oz_helm(oa, st));
     } else if (plane_form) {
       // K_z p by the z pass, then (K_x + K_y) p added plane by plane
-      WVL_CHK(q.pass(OP_CK, 3, Pv, Q, nullptr, 1.0, ez));
+      WVL_CHK(z_pass(it));
       Mark mk(p, st, ST_HELM);
       if (use_line(p)) {
         XyArgs xa = xy_args(p, ws);
@@ -1623,7 +1634,7 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
     } else if (!separate) {
       // combined filter (analysis o kinetic o synthesis) per axis, on the
       // coefficients; q = Kin p here, the shift is applied in the update
-      WVL_CHK(q.pass(OP_CK, 3, Pv, Q, nullptr, 1.0, ez));
+      WVL_CHK(z_pass(it));
       WVL_CHK(q.pass(OP_CK, 2, Pv, Q, Q, 1.0, ey));
       WVL_CHK(q.pass(OP_CK, 1, Pv, Q, Q, 1.0, ex));
     } else {
@@ -1639,24 +1650,25 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
     {
       Mark mk(p, st, ST_CG);
       if (p->bc_line && !(mode & WVL_PRECOND_PASSES))
-        WVL_CHK(launch_cg_alpha(p->norb, p->d_pb + 2 * (p->norb + 1), p->d_pq, nullptr, p->d_pc, ez,
+        WVL_CHK(launch_cg_alpha(p->norb, p->d_pb + 2 * (p->norb + 1), p->d_pq, nullptr, p->d_pc, ppre, ez,
                                 (double*)wsp(ws, p->o_kpl), nullptr, prz, ppp, eps_d, sc, st));
       else if (p->bc_any)
         WVL_CHK(launch_cg_alpha(p->norb, p->d_pb + 2 * (p->norb + 1), p->d_pb + (p->norb + 1), p->d_pb,
-                                p->d_pc, ez, ey, ex, prz, ppp, eps_d, sc, st));
+                                p->d_pc, ppre, ez, ey, ex, prz, ppp, eps_d, sc, st));
       else if (exact)
-        WVL_CHK(launch_cg_alpha(p->norb, p->d_pxz, p->d_pq, nullptr, p->d_pc, oa.ez, kpl, nullptr,
+        WVL_CHK(launch_cg_alpha(p->norb, p->d_pxz, p->d_pq, nullptr, p->d_pc, ppre, oa.ez, kpl, nullptr,
                                 prz, ppp, eps_d, sc, st));
       else if (plane_form)
-        WVL_CHK(launch_cg_alpha(p->norb, p->d_pz, p->d_pq, nullptr, p->d_pc, ez, kpl, nullptr, prz,
+        WVL_CHK(launch_cg_alpha(p->norb, p->d_pz, p->d_pq, nullptr, p->d_pc, ppre, ez, kpl, nullptr, prz,
                                 ppp, eps_d, sc, st));
       else
         WVL_CHK(launch_cg_alpha(p->norb, p->d_pz, p->d_py, p->xdiv == 2 ? p->d_px2 : p->d_px,
-                                p->d_pc, ez, ey, ex, prz, ppp, eps_d, sc, st));
+                                p->d_pc, ppre, ez, ey, ex, prz, ppp, eps_d, sc, st));
       WVL_CHK(launch_cg_update1(p->prec, gp, nt, gt, R, Pv, Q, eps_d, separate ? 0 : 1, sc, plane,
                                 prz, prr, st));
+      if (it + 1 == iters) break;   // no further direction
       WVL_CHK(launch_cg_beta(p->norb, p->d_pc, prz, sc, st));
-      WVL_CHK(launch_cg_update2(p->prec, gp, nt, R, Pv, eps_d, sc, plane, ppp, st));
+      if (!fused) WVL_CHK(launch_cg_update2(p->prec, gp, nt, R, Pv, eps_d, sc, plane, ppp, st));
     }
   }
   if (res) WVL_CHK(launch_cg_res(p->norb, p->d_pc, prr, res, st));

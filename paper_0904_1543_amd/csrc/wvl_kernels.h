@@ -64,8 +64,13 @@ int cg_tile_elems();
 hipError_t launch_cg_init(int prec, const PassGeom& g, int ntiles, const void* gin, void* x,
                           void* r, void* p, const double* eps, int64_t plane, double* prz,
                           double* ppp, double* prr, hipStream_t st);
+struct CgScal { double alpha, beta, rz, pad; };   // per orbital
+hipError_t launch_cg_z(int prec, const PassGeom& g, int ntiles, const void* r, const void* pold,
+                       void* pnew, void* q, const double* eps, const void* sc, int64_t plane,
+                       double* epart, double* ppart, hipStream_t st);
+// prefixes: of the kinetic partials, of rz (pr) and of pp (ppre)
 hipError_t launch_cg_alpha(int norb, const int32_t* pz, const int32_t* py, const int32_t* px,
-                           const int32_t* pp, const double* ez, const double* ey, const double* ex,
+                           const int32_t* pr, const int32_t* ppre, const double* ez, const double* ey, const double* ex,
                            const double* prz, const double* ppp, const double* eps, void* sc,
                            hipStream_t st);
 hipError_t launch_cg_update1(int prec, const PassGeom& g, int ntiles, void* x, void* r,

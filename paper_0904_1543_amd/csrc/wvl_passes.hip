@@ -12,6 +12,21 @@ template <int P>
 hipError_t zfinal_p(const PassGeom& g, int ntiles, const void* t, const void* c, const void* kxy,
                     void* out, int64_t plane, double kmul, double* epart, hipStream_t st);
 
+template <int P>
+hipError_t cg_z_p(const PassGeom& g, int ntiles, const void* r, const void* pold, void* pnew, void* q,
+                  const double* eps, const void* sc, int64_t plane, double* epart, double* ppart,
+                  hipStream_t st);
+
+hipError_t launch_cg_z(int prec, const PassGeom& g, int ntiles, const void* r, const void* pold,
+                       void* pnew, void* q, const double* eps, const void* sc, int64_t plane,
+                       double* epart, double* ppart, hipStream_t st) {
+  switch (prec) {
+    case F64: return cg_z_p<F64>(g, ntiles, r, pold, pnew, q, eps, sc, plane, epart, ppart, st);
+    case F32: return cg_z_p<F32>(g, ntiles, r, pold, pnew, q, eps, sc, plane, epart, ppart, st);
+    default:  return cg_z_p<F32C>(g, ntiles, r, pold, pnew, q, eps, sc, plane, epart, ppart, st);
+  }
+}
+
 hipError_t launch_zfinal(int prec, const PassGeom& g, int ntiles, const void* t, const void* c,
                          const void* kxy, void* out, int64_t plane, double kmul, double* epart,
                          hipStream_t st) {

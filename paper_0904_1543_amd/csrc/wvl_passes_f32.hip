@@ -6,4 +6,6 @@ template hipError_t launch_op<F32>(int, int, const PassGeom&, int, const void*, 
                                   int64_t, double, double*, hipStream_t);
 template hipError_t zfinal_p<F32>(const PassGeom&, int, const void*, const void*, const void*, void*,
                                  int64_t, double, double*, hipStream_t);
+template hipError_t cg_z_p<F32>(const PassGeom&, int, const void*, const void*, void*, void*,
+                               const double*, const void*, int64_t, double*, double*, hipStream_t);
 }  // namespace wvl

@@ -9,7 +9,8 @@
 //   alpha    per orbital: alpha = (r.z) / (p.q), with p.q = p.Kin p - eps p.p
 //   update1  x += alpha p, r -= alpha q, z = r / diag
 //   beta     per orbital: beta = (r.z)_new / (r.z)_old
-//   update2  p = z + beta p
+//   update2  p = z + beta p (on the periodic combined-filter forms inside the
+//            next z pass: wvl_passes_impl.h)
 // The Jacobi preconditioner diag is the diagonal of the operator in the
 // wavelet basis: per axis one value for scaling and one for wavelet
 // coefficients (OrbDev::kdiag), minus eps.  Every element kernel reads and
@@ -20,8 +21,6 @@
 #include "wvl_kernels.h"
 
 namespace wvl {
-
-struct CgScal { double alpha, beta, rz, pad; };
 
 // Tiles of the element kernels: kCgTile consecutive elements of one orbital.
 // A thread moves groups of four consecutive elements (one 16-byte access per
@@ -201,15 +200,15 @@ __device__ __forceinline__ double orb_sum(const double* part, const int32_t* pre
 
 // one workgroup per orbital: p.q = (kinetic partials of the passes) - eps p.p
 __global__ __launch_bounds__(kThreads) void k_cg_alpha(const int32_t* pz, const int32_t* py,
-                                                       const int32_t* px, const int32_t* pp,
-                                                       const double* ez, const double* ey,
+                                                       const int32_t* px, const int32_t* pr,
+                                                       const int32_t* ppre, const double* ez, const double* ey,
                                                        const double* ex, const double* prz,
                                                        const double* ppp, const double* eps,
                                                        CgScal* sc) {
   const int b = blockIdx.x;
   const double kin = orb_sum(ez, pz, b) + orb_sum(ey, py, b) + orb_sum(ex, px, b);
-  const double rz = orb_sum(prz, pp, b);
-  const double pn = orb_sum(ppp, pp, b);
+  const double rz = orb_sum(prz, pr, b);
+  const double pn = orb_sum(ppp, ppre, b);
   if (threadIdx.x == 0) {
     const double pq = kin - eps[b] * pn;
     sc[b].alpha = (pq > 0.0 && rz > 0.0) ? rz / pq : 0.0;
@@ -381,11 +380,11 @@ hipError_t launch_cg_init(int prec, const PassGeom& g, int ntiles, const void* g
 }
 
 hipError_t launch_cg_alpha(int norb, const int32_t* pz, const int32_t* py, const int32_t* px,
-                           const int32_t* pp, const double* ez, const double* ey, const double* ex,
-                           const double* prz, const double* ppp, const double* eps, void* sc,
+                           const int32_t* pr, const int32_t* ppre, const double* ez,
+                           const double* ey, const double* ex, const double* prz, const double* ppp, const double* eps, void* sc,
                            hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_alpha, dim3(norb), dim3(kThreads), 0, st, pz, py, px, pp, ez, ey, ex, prz,
-                     ppp, eps, (CgScal*)sc);
+  hipLaunchKernelGGL(k_cg_alpha, dim3(norb), dim3(kThreads), 0, st, pz, py, px, pr, ppre, ez, ey, ex,
+                     prz, ppp, eps, (CgScal*)sc);
   return hipGetLastError();
 }
 
