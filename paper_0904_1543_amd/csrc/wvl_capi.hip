@@ -761,6 +761,7 @@ struct Seq {
   Seq(wvl_plan* pl, hipStream_t s) : p(pl), st(s) {
     gz = PassGeom{p->d_orbs, p->d_pz, p->norb};
     gz.zlen = p->zlen;
+    gz.stream = p->elems * 8 > kCacheBytes;   // (float64 only)
     gy = PassGeom{p->d_orbs, p->d_py, p->norb};
     gx = PassGeom{p->d_orbs, p->xdiv == 2 ? p->d_px2 : p->d_px, p->norb};
     gx.xdiv = p->xdiv;

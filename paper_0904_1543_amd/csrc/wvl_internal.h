@@ -128,6 +128,7 @@ struct PassGeom {
   int32_t grid;
   int32_t xdiv;    // axis-1 passes: rows per tile = (rows that fit in LDS) / xdiv
   int32_t occ_weight;   // kinetic passes: weight the output by the orbital's occupation
+  int32_t stream;       // results past the caches
   int32_t zlen;         // axis-3 passes: outputs of a line per lane (even)
 };
 
@@ -199,6 +200,19 @@ __device__ __forceinline__ int wrapi(int i, int m) {
   return i < 0 ? i + m : i;
 }
 
+// Store of a result that the launch does not read again, past the caches: the
+// arrays being read keep them.  Pays for 8-byte values (local H*psi of 256
+// float64 orbitals of 48^3 cells 5.45 -> 5.28 ms; single and paired floats,
+// whose waves store half as much at a time, lose 1.5%).  A z pass whose result
+// the next launch reads takes it only where the array would not stay in the
+// 256 MB cache anyway (PassGeom::stream: density of 16 such orbitals, 113 MB,
+// 143 us with plain stores and 151 without; 128 orbitals of 32^3 cells,
+// 268 MB, 236 and 231).
+template <typename V> __device__ __forceinline__ void stream_st(V* p, V v) {
+  __builtin_nontemporal_store(v, p);
+}
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+
 // ---------------------------------------------------------------------------
 // Precision traits.  V is the register value; storage is planar.
 // ---------------------------------------------------------------------------
@@ -222,6 +236,7 @@ template <> struct Prec<F64> {
   static constexpr int bytes = 8;
   __device__ static V ldc(const void* p, int64_t i, int64_t) { return ((const double*)p)[i]; }
   __device__ static void st(void* p, int64_t i, int64_t, V v) { ((double*)p)[i] = v; }
+  __device__ static void st_stream(void* p, int64_t i, int64_t, V v) { stream_st((double*)p + i, v); }
   __device__ static Acc zero() { return Acc{0.0}; }
   template <int OP> __device__ static void add(Acc& a, int par, int o, const V& x) {
     a.s = __builtin_fma(coef<OP>(par, o, 0), x, a.s);
@@ -239,6 +254,7 @@ template <> struct Prec<F32> {
   static constexpr int bytes = 4;
   __device__ static V ldc(const void* p, int64_t i, int64_t) { return ((const float*)p)[i]; }
   __device__ static void st(void* p, int64_t i, int64_t, V v) { ((float*)p)[i] = v; }
+  __device__ static void st_stream(void* p, int64_t i, int64_t plane, V v) { st(p, i, plane, v); }
   __device__ static Acc zero() { return Acc{0.0f}; }
   template <int OP> __device__ static void add(Acc& a, int par, int o, const V& x) {
     a.s = __builtin_fmaf((float)coef<OP>(par, o, 1), x, a.s);
@@ -270,6 +286,7 @@ template <> struct Prec<F32C> {
     f[i] = h;
     f[plane + i] = (float)(v - (double)h);
   }
+  __device__ static void st_stream(void* p, int64_t i, int64_t plane, V v) { st(p, i, plane, v); }
   __device__ static Acc zero() { return Acc{0.0}; }
   template <int OP> __device__ static void add(Acc& a, int par, int o, const V& x) {
     a.s = __builtin_fma(coef<OP>(par, o, 0), x, a.s);

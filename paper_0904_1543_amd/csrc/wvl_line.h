@@ -50,13 +50,13 @@ template <> struct LineIO<F64> {
   }
   __device__ static void cvt(const Raw& r, C& a, C& b) { a = r.v.x; b = r.v.y; }
   __device__ static void st2(char* p, uint32_t i, int64_t, C a, C b) {
-    *reinterpret_cast<d2u*>(p + 8u * i) = d2u{a, b};
+    stream_st(reinterpret_cast<d2u*>(p + 8u * i), d2u{a, b});
   }
   __device__ static C ld(const char* p, uint32_t i, int64_t) {
     return *reinterpret_cast<const double*>(p + 8u * i);
   }
   __device__ static void st(char* p, uint32_t i, int64_t, C v) {
-    *reinterpret_cast<double*>(p + 8u * i) = v;
+    stream_st(reinterpret_cast<double*>(p + 8u * i), v);
   }
 };
 template <> struct LineIO<F32> {

@@ -59,7 +59,7 @@ __device__ __forceinline__ int64_t z_segment(int t, int64_t L, int m, int zlen, 
 // ---------------------------------------------------------------------------
 // Strided-axis pass (AXIS = 2 or 3)
 // ---------------------------------------------------------------------------
-template <int OP, int P, int AXIS, bool K0, bool EN>
+template <int OP, int P, int AXIS, bool K0, bool EN, bool STREAM = false>
 __global__ __launch_bounds__(kThreads) void k_strided(PassGeom g, const void* __restrict__ in,
                                                       void* __restrict__ out, const void* k0,
                                                       int64_t plane, double kmul,
@@ -138,8 +138,13 @@ __global__ __launch_bounds__(kThreads) void k_strided(PassGeom g, const void* __
             y0 = T::plus(y0, c0);
             y1 = T::plus(y1, c1);
           }
-          T::st(out, i0, plane, y0);
-          T::st(out, i1, plane, y1);
+          if (STREAM) {
+            T::st_stream(out, i0, plane, y0);
+            T::st_stream(out, i1, plane, y1);
+          } else {
+            T::st(out, i0, plane, y0);
+            T::st(out, i1, plane, y1);
+          }
           #pragma unroll
           for (int i = 0; i < W - 1; ++i) win[i] = win[i + 2];
         }
@@ -219,8 +224,8 @@ __global__ __launch_bounds__(kThreads) void k_zfinal(PassGeom g, const void* __r
           z1 = T::plus(z1, x1);
           pair_conv<P, OP_CWT>(wt, y0, y1);
           const int64_t i0 = base + (int64_t)kk * stride;
-          T::st(out, i0, plane, T::plus(y0, z0));
-          T::st(out, i0 + stride, plane, T::plus(y1, z1));
+          T::st_stream(out, i0, plane, T::plus(y0, z0));
+          T::st_stream(out, i0 + stride, plane, T::plus(y1, z1));
           #pragma unroll
           for (int i = 0; i < WT - 1; ++i) wt[i] = wt[i + 2];
           #pragma unroll
@@ -238,14 +243,14 @@ __global__ __launch_bounds__(kThreads) void k_zfinal(PassGeom g, const void* __r
 //     p = r / diag + beta p_old,   q = K_z p
 // with the partials of p.q and p.p of each tile.  The update is a pass over
 // r and p_old that the z pass reads anyway, so the fused launch moves four
-// arrays where the two moved five: 256 float64 orbitals of 48^3 cells 1.78 ms
-// where the two took 0.93 + 1.02.  p goes to another
+// arrays where the two moved five: 256 float64 orbitals of 48^3 cells 1.53 ms
+// (4.7 TB/s) where the two took 0.93 + 1.02.  p goes to another
 // array than p_old: lanes re-read the ends of a line for the periodic wrap.
 // Loads, not the FMAs, bound it: kPfP pairs of each operand are in flight.
 // ---------------------------------------------------------------------------
 constexpr int kPfP = 2;
 
-template <int P>
+template <int P, bool STREAM>
 __global__ __launch_bounds__(kThreads, 2) void k_cg_z(PassGeom g, const void* __restrict__ r,
                                                       const void* __restrict__ pold,
                                                       void* __restrict__ pnew, void* __restrict__ q,
@@ -319,10 +324,17 @@ __global__ __launch_bounds__(kThreads, 2) void k_cg_z(PassGeom g, const void* __
           e += c0 * T::d(y0) + c1 * T::d(y1);
           pp += c0 * c0 + c1 * c1;
           const int64_t i0 = base + (int64_t)kk * L, i1 = i0 + L;
-          T::st(q, i0, plane, y0);
-          T::st(q, i1, plane, y1);
-          T::st(pnew, i0, plane, win[OHI]);
-          T::st(pnew, i1, plane, win[OHI + 1]);
+          if (STREAM) {
+            T::st_stream(q, i0, plane, y0);
+            T::st_stream(q, i1, plane, y1);
+            T::st_stream(pnew, i0, plane, win[OHI]);
+            T::st_stream(pnew, i1, plane, win[OHI + 1]);
+          } else {
+            T::st(q, i0, plane, y0);
+            T::st(q, i1, plane, y1);
+            T::st(pnew, i0, plane, win[OHI]);
+            T::st(pnew, i1, plane, win[OHI + 1]);
+          }
           #pragma unroll
           for (int i = 0; i < W - 1; ++i) win[i] = win[i + 2];
         }
@@ -411,8 +423,11 @@ static hipError_t launch_axis(int axis, const PassGeom& g, int ntiles, const voi
     if (k0) { if (en) WVL_L((k_strided<OP, P, 2, true, true>)); else WVL_L((k_strided<OP, P, 2, true, false>)); }
     else    { if (en) WVL_L((k_strided<OP, P, 2, false, true>)); else WVL_L((k_strided<OP, P, 2, false, false>)); }
   } else {
+    constexpr bool S = P == F64;   // (stream_st)
     if (k0) { if (en) WVL_L((k_strided<OP, P, 3, true, true>)); else WVL_L((k_strided<OP, P, 3, true, false>)); }
-    else    { if (en) WVL_L((k_strided<OP, P, 3, false, true>)); else WVL_L((k_strided<OP, P, 3, false, false>)); }
+    else if (S && g.stream) {
+      if (en) WVL_L((k_strided<OP, P, 3, false, true, S>)); else WVL_L((k_strided<OP, P, 3, false, false, S>));
+    } else  { if (en) WVL_L((k_strided<OP, P, 3, false, true>)); else WVL_L((k_strided<OP, P, 3, false, false>)); }
   }
 #undef WVL_L
   return hipGetLastError();
@@ -452,8 +467,12 @@ hipError_t cg_z_p(const PassGeom& g, int ntiles, const void* r, const void* pold
                   const double* eps, const void* sc, int64_t plane, double* epart, double* ppart,
                   hipStream_t st) {
   if (ntiles == 0) return hipSuccess;
-  hipLaunchKernelGGL((k_cg_z<P>), dim3(ntiles), dim3(kThreads), 0, st, g, r, pold, pnew, q, eps,
-                     (const CgScal*)sc, plane, epart, ppart);
+  if (P == F64 && g.stream)
+    hipLaunchKernelGGL((k_cg_z<P, P == F64>), dim3(ntiles), dim3(kThreads), 0, st, g, r, pold, pnew, q,
+                       eps, (const CgScal*)sc, plane, epart, ppart);
+  else
+    hipLaunchKernelGGL((k_cg_z<P, false>), dim3(ntiles), dim3(kThreads), 0, st, g, r, pold, pnew, q,
+                       eps, (const CgScal*)sc, plane, epart, ppart);
   return hipGetLastError();
 }
 

@@ -1,7 +1,8 @@
-"""The z passes with their lines cut into segments (one orbital; segments that do
-not divide the line; whole lines for many orbitals), against the float64 oracle
-with the tolerances of the parity tests: local H*psi, kinetic energies and the
-preconditioner over the same batches."""
+"""The z passes where their launches change form, against the float64 oracle
+with the tolerances of the parity tests: lines cut into segments (one orbital;
+segments that do not divide the line; whole lines for many orbitals), the
+preconditioner's direction update inside the z pass over the same batches, and
+float64 batch arrays larger than the last cache, whose results bypass it."""
 
 import numpy as np
 import pytest
@@ -38,3 +39,8 @@ def _check(prec, norb, dims, some, iters, seed):
 @pytest.mark.parametrize("prec", ["f64", "f32", "f32c"])
 def test_segments_of_lines(prec, norb):
     _check(prec, norb, (16, 16, 9), sorted({0, norb // 2, norb - 1}), 3, 97)
+
+
+def test_batch_larger_than_the_last_cache():
+    """320 orbitals of 0.86 MB each."""
+    _check("f64", 320, (24, 20, 28), [0, 160, 319], 3, 98)
