@@ -66,9 +66,9 @@ typedef enum { WVL_F64 = 0, WVL_F32 = 1, WVL_F32C = 2 } wvl_prec;
 /* plan flags */
 #define WVL_SHARED_V   1u  /* all orbitals share one potential (and one grid)   */
 #define WVL_USE_GRAPH  2u  /* record wvl_local_hpsi in a hipGraph and replay it  */
-/* WVL_PERSISTENT: every pass launch of wvl_local_hpsi (z, y and x passes,
- * the per-orbital potential stage and, without WVL_SHARED_V, the in-plane
- * kernel) runs as a persistent launch: a fixed number of workgroups take
+/* WVL_PERSISTENT: every pass launch of wvl_local_hpsi (y and x passes, z
+ * passes of lines longer than 144 values, the per-orbital potential stage and,
+ * without WVL_SHARED_V, the in-plane kernel) runs as a persistent launch: a fixed number of workgroups take
  * tiles from a work queue, largest orbitals first (longest-processing-time-
  * first order), which balances batches of uneven orbitals.  The queue
  * counters live in the workspace, so calls that share a workspace must not

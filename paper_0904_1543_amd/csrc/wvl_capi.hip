@@ -106,6 +106,12 @@ struct wvl_plan {
   std::vector<OrbDev> orbs;
   std::vector<int32_t> pz, py, px, pp, pq, pc;
   int zlen = 0;          // outputs per lane of the axis-3 passes
+  // z passes of the combined filters with whole lines in LDS (wvl_line_z.h):
+  // classes of orbitals with one launch shape, as ranges of perm_z / order_l
+  // (none: the strided passes), and the prefix of the tiles of 16 lines
+  struct ZClass { int first, n, shape, rows, tiles; };
+  std::vector<ZClass> zl;
+  std::vector<int32_t> pl, order_l;
   int nblk = 0;          // 256-point blocks of the shared grid
   // plane-resident path of wvl_local_hpsi
   bool use_xy = false;
@@ -138,6 +144,8 @@ struct wvl_plan {
   // device copies
   OrbDev* d_orbs = nullptr;
   int32_t* d_pz = nullptr;
+  int32_t* d_pl = nullptr;
+  int32_t* d_order_l = nullptr;
   int32_t* d_py = nullptr;
   int32_t* d_px = nullptr;
   int32_t* d_pp = nullptr;
@@ -245,7 +253,7 @@ static CgLayout cg_layout(const wvl_plan* p) {
   CgLayout l;
   l.rz = 0;
   l.pp = np;
-  l.rr = l.pp + std::max(np, align256(sizeof(double) * (size_t)p->pz[p->norb]));
+  l.rr = l.pp + std::max(np, align256(sizeof(double) * (size_t)std::max(p->pz[p->norb], p->pl[p->norb])));
   l.eps = l.rr + np;
   l.sc = l.eps + align256(sizeof(double) * (size_t)p->norb);
   l.bytes = l.sc + align256(cg_scalar_bytes() * (size_t)p->norb);
@@ -465,6 +473,23 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
       return fail(WVL_EINVAL, "too many tiles");
     }
   }
+  // z passes with whole lines in LDS: for lines that have a shape, in orbitals
+  // that 32-bit byte offsets reach; any size of batch (one orbital of 16^3
+  // cells: 10 + 15 us -> 5 + 9)
+  p->pl.assign(norb + 1, 0);
+  if (!p->bc_any) {
+    bool ok = true;
+    int64_t tiles = 0;
+    for (const OrbDev& d : p->orbs) {
+      tiles += ((int64_t)d.m[0] * d.m[1] + 15) / 16 + kZWaves;
+      ok = ok && (int64_t)d.m[0] * d.m[1] * d.m[2] < (int64_t)1 << 28 && line_z_shape(d.m[2]) >= 0;
+    }
+    ok = ok && tiles < (int64_t)1 << 30;
+    for (int b = 0; b < norb; ++b) {
+      const int64_t n = ((int64_t)p->orbs[b].m[0] * p->orbs[b].m[1] + 15) / 16;
+      p->pl[b + 1] = p->pl[b] + (ok ? (int32_t)((n + kZWaves - 1) / kZWaves * kZWaves) : 0);
+    }
+  }
   p->nblk = p->shared ? (int)((p->Mrs + kThreads - 1) / kThreads) : 0;
   // plane-resident path: every orbital's (m1, m2) plane must fit the kernel
   {
@@ -533,6 +558,20 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
       for (int r = 0; r < norb; ++r) order[r + 1] = order[r] + (pre[perm[r] + 1] - pre[perm[r]]);
     };
     build(p->perm_z, p->order_z, p->pz, [&](int b) { return (int64_t)p->orbs[b].m[2]; });
+    std::vector<int32_t> perm_l;   // = perm_z
+    build(perm_l, p->order_l, p->pl, [&](int b) { return (int64_t)p->orbs[b].m[2]; });
+    // one launch per shape where a batch has several and fills the chip with
+    // them (512 orbitals of 32..128 points per axis in float pairs: H*psi 10.1
+    // -> 9.2 ms); otherwise the longest line's for all
+    const bool split = p->order_l[norb] >= 8 * kZWaves * kZTiles;
+    for (int r = 0; r < norb && p->pl[norb] > 0; ++r) {
+      const int m = p->orbs[perm_l[r]].m[2];
+      if (r == 0 || (split && line_z_shape(m) != p->zl.back().shape))
+        p->zl.push_back({r, 0, line_z_shape(m), m, 0});
+      auto& k = p->zl.back();
+      ++k.n;
+      k.tiles = p->order_l[r + 1] - p->order_l[k.first];
+    }
     // (planes: by launch shape of the plane kernel first)
     auto shape = [&](int b) { return line_shape_of(prec, p->orbs[b].m[0], p->orbs[b].m[1]); };
     build(p->perm_q, p->order_q, p->pq, [&](int b) {
@@ -581,7 +620,8 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
   p->o_D = off; off += arr;      // fourth batch array: preconditioner, separate-pass form
   p->o_cg = off;                 // preconditioner: r.z, p.p, r.r tile partials, eps, scalars
   off += cg_bytes(p);
-  p->o_ez = off; off += align256(sizeof(double) * std::max<int64_t>(p->pz[norb], (int64_t)norb * p->bc_tiles[2]));
+  p->o_ez = off; off += align256(sizeof(double) * std::max<int64_t>(std::max(p->pz[norb], p->pl[norb]),
+                                                                   (int64_t)norb * p->bc_tiles[2]));
   p->o_ey = off; off += align256(sizeof(double) * std::max<int64_t>(p->py[norb], (int64_t)norb * p->bc_tiles[1]));
   p->o_ex = off; off += align256(sizeof(double) * std::max<int64_t>(std::max(p->px[norb], p->px2[norb]),
                                                                    (int64_t)norb * p->bc_tiles[0]));
@@ -621,7 +661,7 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
   if (!ctx->dry) {
     hipError_t e = hipSetDevice(ctx->device);
     if (e == hipSuccess) e = dev_malloc((void**)&p->d_orbs, sizeof(OrbDev) * norb);
-    if (e == hipSuccess) e = dev_malloc((void**)&p->d_pz, sizeof(int32_t) * (norb + 1) * 19);
+    if (e == hipSuccess) e = dev_malloc((void**)&p->d_pz, sizeof(int32_t) * (norb + 1) * 21);
     if (e == hipSuccess) e = dev_malloc((void**)&p->d_info, sizeof(int) * 4);
     if (e != hipSuccess) {
       wvl_plan_destroy(p);
@@ -645,6 +685,8 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
     p->d_order_p = p->d_perm_p + (norb + 1);
     p->d_pc = p->d_order_p + (norb + 1);
     p->d_pxz = p->d_pc + (norb + 1);
+    p->d_pl = p->d_pxz + (norb + 1);
+    p->d_order_l = p->d_pl + (norb + 1);
     std::vector<int32_t> all;
     all.insert(all.end(), p->pz.begin(), p->pz.end());
     all.insert(all.end(), p->py.begin(), p->py.end());
@@ -653,7 +695,7 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
     all.insert(all.end(), p->pq.begin(), p->pq.end());
     for (auto* v : {&p->perm_z, &p->order_z, &p->perm_q, &p->order_q, &p->px2, &p->perm_y,
                     &p->order_y, &p->perm_x, &p->order_x, &p->order_x2, &p->perm_p, &p->order_p,
-                    &p->pc, &p->pxz}) {
+                    &p->pc, &p->pxz, &p->pl, &p->order_l}) {
       all.insert(all.end(), v->begin(), v->end());
       all.resize(all.size() + (norb + 1 - v->size()), 0);
     }
@@ -781,9 +823,39 @@ struct Seq {
     g.grid = p->pgrid_pass;
     return true;
   }
+  // prefix of the energy partials of K along z
+  const int32_t* ck_prefix() const { return p->zl.empty() ? p->d_pz : p->d_pl; }
+  // a z pass with whole lines in LDS
+  hipError_t line_z(int mode, ZLineArgs a) {
+    a.plane = p->elems;
+    hipError_t e = hipSuccess;
+    for (const auto& k : p->zl) {
+      if (e != hipSuccess) break;
+      PassGeom g = gz;
+      const int n = k.tiles / kZWaves;
+      g.prefix = p->d_pl;
+      if (p->zl.size() > 1) {
+        g.order = p->d_order_l + k.first;
+        g.perm = p->d_perm_z + k.first;
+        g.norb = k.n;
+      }
+      a.rows = k.rows;
+      e = launch_line_z(p->prec, mode, k.shape, g, a, n, st);
+    }
+    return e;
+  }
   hipError_t pass(int op, int axis, const void* in, void* out, const void* k0 = nullptr,
                   double kmul = 1.0, double* ep = nullptr) {
     Mark mk(p, st, stage_of(op, axis));
+    if (axis == 3 && !p->zl.empty() && (op == OP_CW || op == OP_CWT || op == OP_CK)) {
+      ZLineArgs a{};
+      a.in = in;
+      a.out = out;
+      a.k0 = k0;
+      a.kmul = kmul;
+      a.epart = ep;
+      return line_z(op == OP_CW ? ZL_CW : op == OP_CWT ? ZL_CWT : ZL_CK, a);
+    }
     PassGeom g = axis == 1 ? gx : axis == 2 ? gy : gz;
     const int n = ntiles(axis);
     if (queue) {
@@ -803,6 +875,16 @@ struct Seq {
   hipError_t zfinal(const void* t, const void* c, const void* kxy, void* out, double kmul,
                     double* ep) {
     Mark mk(p, st, ST_ZFIN);
+    if (!p->zl.empty()) {
+      ZLineArgs a{};
+      a.in = c;
+      a.t = t;
+      a.k0 = kxy;
+      a.out = out;
+      a.kmul = kmul;
+      a.epart = ep;
+      return line_z(ZL_FINAL, a);
+    }
     PassGeom g = gz;
     const int n = p->pz[p->norb];
     if (queue) make_persistent(g, n, p->d_order_z, p->d_perm_z);
@@ -1193,7 +1275,7 @@ int hpsi_sequence(wvl_plan* p, hipStream_t st, const void* c, const double* V, d
     if (want_e) {
       Mark mk(p, st, ST_ENERGY);
       // kinetic: z-pass tiles + per-plane in-plane sums; potential: per plane
-      WVL_CHK(launch_orb_sums(p->d_orbs, p->norb, p->d_pz, p->d_pq, nullptr, ez, kpl, nullptr, epl,
+      WVL_CHK(launch_orb_sums(p->d_orbs, p->norb, q.ck_prefix(), p->d_pq, nullptr, ez, kpl, nullptr, epl,
                               1, p->d_pq, 0, eorb, st));
       if (e_loc || e_kin)
         WVL_CHK(launch_totals(p->d_orbs, p->norb, eorb, rv, p->shared ? p->nblk : 0, e_loc, e_kin, st));
@@ -1228,7 +1310,7 @@ int hpsi_sequence(wvl_plan* p, hipStream_t st, const void* c, const double* V, d
   if (want_e) {
     Mark mk(p, st, ST_ENERGY);
     const int pot_mode = p->shared ? (e_orb ? 2 : 0) : 1;
-    WVL_CHK(launch_orb_sums(p->d_orbs, p->norb, p->d_pz, p->d_py,
+    WVL_CHK(launch_orb_sums(p->d_orbs, p->norb, q.ck_prefix(), p->d_py,
                             p->xdiv == 2 ? p->d_px2 : p->d_px, ez, ey, ex, pp, pot_mode,
                             p->d_pp, p->nblk, eorb, st));
     if (e_loc || e_kin)
@@ -1598,8 +1680,21 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
   auto z_pass = [&](int it) {
     if (it == 0) return q.pass(OP_CK, 3, Pv, Q, nullptr, 1.0, ez);
     Mark mk(p, st, stage_of(OP_CK, 3));
-    ppre = p->d_pz;
+    ppre = q.ck_prefix();
     std::swap(Pv, D);
+    if (!p->zl.empty()) {
+      ZLineArgs a{};
+      a.in = D;
+      a.r = R;
+      a.pnew = Pv;
+      a.out = Q;
+      a.eps = eps_d;
+      a.sc = (const CgScal*)sc;
+      a.kmul = 1.0;
+      a.epart = ez;
+      a.ppart = ppp;
+      return q.line_z(ZL_CG, a);
+    }
     return launch_cg_z(p->prec, q.gz, p->pz[p->norb], R, D, Pv, Q, eps_d, sc, plane, ez, ppp, st);
   };
   for (int it = 0; it < iters; ++it) {
@@ -1660,10 +1755,11 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
         WVL_CHK(launch_cg_alpha(p->norb, p->d_pxz, p->d_pq, nullptr, p->d_pc, ppre, oa.ez, kpl, nullptr,
                                 prz, ppp, eps_d, sc, st));
       else if (plane_form)
-        WVL_CHK(launch_cg_alpha(p->norb, p->d_pz, p->d_pq, nullptr, p->d_pc, ppre, ez, kpl, nullptr, prz,
+        WVL_CHK(launch_cg_alpha(p->norb, q.ck_prefix(), p->d_pq, nullptr, p->d_pc, ppre, ez, kpl, nullptr, prz,
                                 ppp, eps_d, sc, st));
       else
-        WVL_CHK(launch_cg_alpha(p->norb, p->d_pz, p->d_py, p->xdiv == 2 ? p->d_px2 : p->d_px,
+        WVL_CHK(launch_cg_alpha(p->norb, separate ? p->d_pz : q.ck_prefix(), p->d_py,
+                                p->xdiv == 2 ? p->d_px2 : p->d_px,
                                 p->d_pc, ppre, ez, ey, ex, prz, ppp, eps_d, sc, st));
       WVL_CHK(launch_cg_update1(p->prec, gp, nt, gt, R, Pv, Q, eps_d, separate ? 0 : 1, sc, plane,
                                 prz, prr, st));

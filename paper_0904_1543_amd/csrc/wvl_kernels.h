@@ -65,6 +65,26 @@ hipError_t launch_cg_init(int prec, const PassGeom& g, int ntiles, const void* g
                           void* r, void* p, const double* eps, int64_t plane, double* prz,
                           double* ppp, double* prr, hipStream_t st);
 struct CgScal { double alpha, beta, rz, pad; };   // per orbital
+// z passes with whole lines in LDS (wvl_line_z.h): g.prefix counts tiles of 16
+// lines, padded per orbital to the kZWaves of a workgroup; one partial sum per
+// tile.  rows: longest line.
+struct ZLineArgs {
+  const void* in;        // c; ZL_CG: p of the step before (r null: p itself)
+  const void* t;         // ZL_FINAL
+  const void* k0;        // nullable (not ZL_FINAL's): added
+  const void* r;         // ZL_CG
+  void* out;
+  void* pnew;            // ZL_CG
+  const double* eps;
+  const CgScal* sc;
+  int64_t plane;
+  double kmul;
+  double* epart;         // nullable
+  double* ppart;
+  int32_t rows;
+};
+hipError_t launch_line_z(int prec, int mode, int shape, const PassGeom& g, const ZLineArgs& a,
+                         int nblocks, hipStream_t st);
 hipError_t launch_cg_z(int prec, const PassGeom& g, int ntiles, const void* r, const void* pold,
                        void* pnew, void* q, const double* eps, const void* sc, int64_t plane,
                        double* epart, double* ppart, hipStream_t st);

@@ -58,6 +58,9 @@ template <> struct LineIO<F64> {
   __device__ static void st(char* p, uint32_t i, int64_t, C v) {
     stream_st(reinterpret_cast<double*>(p + 8u * i), v);
   }
+  __device__ static void st_keep(char* p, uint32_t i, int64_t, C v) {
+    *reinterpret_cast<double*>(p + 8u * i) = v;
+  }
 };
 template <> struct LineIO<F32> {
   using C = float;
@@ -78,6 +81,7 @@ template <> struct LineIO<F32> {
   __device__ static void st(char* p, uint32_t i, int64_t, C v) {
     *reinterpret_cast<float*>(p + 4u * i) = v;
   }
+  __device__ static void st_keep(char* p, uint32_t i, int64_t, C v) { st(p, i, 0, v); }
 };
 template <> struct LineIO<F32C> {
   using C = double;
@@ -106,6 +110,7 @@ template <> struct LineIO<F32C> {
     S::st(p, i, 0, h);
     S::st(p + 4 * plane, i, 0, (float)(v - (double)h));
   }
+  __device__ static void st_keep(char* p, uint32_t i, int64_t plane, C v) { st(p, i, plane, v); }
 };
 
 // f(integral constant) for 0 .. N - 1: filter taps and window offsets are

@@ -2,6 +2,7 @@
 // wvl_passes_impl.h, instantiated per precision by wvl_passes_<prec>.hip).
 
 #include "wvl_kernels.h"
+#include "wvl_plane.h"
 
 namespace wvl {
 
@@ -34,6 +35,31 @@ hipError_t launch_zfinal(int prec, const PassGeom& g, int ntiles, const void* t,
     case F64: return zfinal_p<F64>(g, ntiles, t, c, kxy, out, plane, kmul, epart, st);
     case F32: return zfinal_p<F32>(g, ntiles, t, c, kxy, out, plane, kmul, epart, st);
     default:  return zfinal_p<F32C>(g, ntiles, t, c, kxy, out, plane, kmul, epart, st);
+  }
+}
+
+template <int P, int MODE>
+hipError_t line_z_launch(int shape, const PassGeom& g, const ZLineArgs& a, int nblocks, hipStream_t st);
+
+template <int P>
+static hipError_t line_z_mode(int mode, int shape, const PassGeom& g, const ZLineArgs& a, int nblocks,
+                              hipStream_t st) {
+  switch (mode) {
+    case ZL_CW:    return line_z_launch<P, ZL_CW>(shape, g, a, nblocks, st);
+    case ZL_CWT:   return line_z_launch<P, ZL_CWT>(shape, g, a, nblocks, st);
+    case ZL_CK:    return line_z_launch<P, ZL_CK>(shape, g, a, nblocks, st);
+    case ZL_FINAL: return line_z_launch<P, ZL_FINAL>(shape, g, a, nblocks, st);
+    default:       return line_z_launch<P, ZL_CG>(shape, g, a, nblocks, st);
+  }
+}
+
+hipError_t launch_line_z(int prec, int mode, int shape, const PassGeom& g, const ZLineArgs& a,
+                         int nblocks, hipStream_t st) {
+  if (nblocks == 0) return hipSuccess;
+  switch (prec) {
+    case F64: return line_z_mode<F64>(mode, shape, g, a, nblocks, st);
+    case F32: return line_z_mode<F32>(mode, shape, g, a, nblocks, st);
+    default:  return line_z_mode<F32C>(mode, shape, g, a, nblocks, st);
   }
 }
 

@@ -97,4 +97,22 @@ __host__ __device__ inline int line_lines(int U, int ns) {
 }
 constexpr int kNumLineShapes = sizeof(kLineShapes) / sizeof(kLineShapes[0]);
 
+// z passes with whole lines in LDS (wvl_line_z.h): W, W^T and K along z, the
+// last z step of H*psi, K with the preconditioner's direction update
+enum { ZL_CW = 0, ZL_CWT = 1, ZL_CK = 2, ZL_FINAL = 3, ZL_CG = 4 };
+// Shapes: lines of up to 4 U mi values (U outputs a segment, mi groups of four
+// segments); the first that fits.  wpe: waves per SIMD that the registers and
+// (last shape) the LDS allow.
+constexpr int kZWaves = 4;   // waves of a workgroup, each 16 lines
+constexpr int kZLines = 16 * kZWaves;
+struct ZShape { int U, mi, wpe; };
+constexpr ZShape kZShapes[] = {{8, 1, 4}, {8, 2, 4}, {10, 2, 3}, {12, 2, 3}, {10, 3, 3},
+                                {12, 3, 2}};
+constexpr int kNumZShapes = sizeof(kZShapes) / sizeof(kZShapes[0]);
+inline int line_z_shape(int m) {
+  for (int s = 0; s < kNumZShapes; ++s)
+    if (m <= 4 * kZShapes[s].U * kZShapes[s].mi) return s;
+  return -1;
+}
+
 }  // namespace wvl
