@@ -532,10 +532,10 @@ struct LineKernel {
     const OrbConst orbs = (OrbConst)a.orbs;
     // u and t of orbital b (isolated axes: m3_rs planes an orbital)
     auto uoff = [&](int b) {
-      return FREE ? (int64_t)b * a.m3_rs * (m1 * m2) + zo : orbs[b].off + zo;
+      return FREE && MODE != LINE_HELM ? (int64_t)b * a.m3_rs * (m1 * m2) + zo : orbs[b].off + zo;
     };
     const int64_t plane_u = FREE && MODE != LINE_HELM ? a.plane_u : a.plane;
-    Raw ru[MI][NPF], rc[MI][NPF];
+    Raw ru[MI][NPF], rc[MI][NPF];   // (HELM: ru is kq)
     #pragma unroll
     for (int i = 0; i < MI; ++i) {
       if (MODE == LINE_HELM) load(a.c, a.plane, orbs[b0].off + zo, i, rc[i], true);
@@ -568,6 +568,13 @@ struct LineKernel {
           put(B, i, rc[i]);
           wave_sync();
           kinetic<1>(B, i, (C)o.ks1, kx[i], ek);
+        }
+      }
+      if (MODE == LINE_HELM) {   // kq and the next plane arrive behind the columns
+        #pragma unroll
+        for (int i = 0; i < MI; ++i) {
+          load(a.kxy, a.plane, gp, i, ru[i], true);
+          load(a.c, a.plane, gn, i, rc[i], more);
         }
       }
       __syncthreads();
@@ -626,6 +633,10 @@ struct LineKernel {
         // in order)
         arrive(KC1 ? rc : ru);
       }
+      if (MODE == LINE_HELM) {
+        arrive(ru);
+        arrive(rc);
+      }
       #pragma unroll
       for (int i = 0; i < MI; ++i) {
         if (count<1>(i) == 0) break;
@@ -633,7 +644,7 @@ struct LineKernel {
           copy_out(A, i, a.t, plane_u, gu);
           if (KC) kxy_out(i, kx[i], km, gp);
         } else {
-          helm_out(i, kx[i], km, gp);
+          helm_out(i, kx[i], km, gp, ru[i]);
         }
       }
       if (KC1) {
@@ -673,9 +684,8 @@ struct LineKernel {
     copy_out(B, i, a.kxy, a.plane, gp);
   }
   // kq = km (kq + (K_x + K_y) p)
-  __device__ __forceinline__ void helm_out(int i, const C (&kx)[U], C km, int64_t gp) const {
-    Raw q[NPF];
-    load(a.kxy, a.plane, gp, i, q, true);
+  __device__ __forceinline__ void helm_out(int i, const C (&kx)[U], C km, int64_t gp,
+                                           const Raw (&q)[NPF]) const {
     each<OP_CK, 1>(i, [&](int u, int pos, int, int) { B[pos] += kx[u]; });
     wave_sync();
     const int np = count<1>(i) * m1 >> 1;
@@ -694,7 +704,8 @@ struct LineKernel {
 
 // Grid: shared potential: blockIdx.x = z * ngroups + g, the orbitals of group
 // g in turn (the density of the group's plane stays in registers and is
-// written once); otherwise one (orbital, a.plane) per tile of the prefix pq.
+// written once; HELM: the next orbital's plane is loaded behind this one's
+// columns); otherwise one (orbital, plane) per tile of the prefix pq.
 template <int P, int PITCH, int U, int MI, bool TWO, int MODE, bool SHARED, int FREE, int NT, int WPE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void k_line(XyArgs a) {
@@ -711,6 +722,7 @@ void k_line(XyArgs a) {
     const int b0 = g * a.G, b1 = min(b0 + a.G, a.norb);
     const K k(a, lds, rd, (OrbConst)a.orbs + b0);
     k.planes(b0, b1, z, rho);
+    if (MODE == LINE_HELM) return;
     double* rp = a.rho_part + (int64_t)g * a.M + (int64_t)z * (k.M1 * k.M2);
     #pragma unroll
     for (int i = 0; i < MI; ++i)

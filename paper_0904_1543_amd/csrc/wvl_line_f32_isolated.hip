@@ -4,5 +4,5 @@
 namespace wvl {
 template hipError_t line_launch<F32, LINE_HPSI, true, 3>(int, const XyArgs&, int, int, size_t, hipStream_t);
 template hipError_t line_launch<F32, LINE_RHO, true, 3>(int, const XyArgs&, int, int, size_t, hipStream_t);
-template hipError_t line_launch<F32, LINE_HELM, false, 3>(int, const XyArgs&, int, int, size_t, hipStream_t);
+template hipError_t line_launch<F32, LINE_HELM, true, 3>(int, const XyArgs&, int, int, size_t, hipStream_t);
 }  // namespace wvl

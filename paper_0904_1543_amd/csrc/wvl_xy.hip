@@ -134,15 +134,15 @@ hipError_t launch_line(int prec, int mode, const XyArgs& a, int m1, int m2, int 
   const int s = line_shape(prec, mode, m1, m2, a.free, &nt, &lds);
   if (s < 0) return hipErrorInvalidValue;
 #define WVL_F(P, FR)                                                                             \
-  (mode == LINE_HELM  ? line_launch<P, LINE_HELM, false, FR>(s, a, nblocks, nt, lds, st)         \
+  (mode == LINE_HELM  ? line_launch<P, LINE_HELM, true, FR>(s, a, nblocks, nt, lds, st)          \
    : mode == LINE_RHO ? line_launch<P, LINE_RHO, true, FR>(s, a, nblocks, nt, lds, st)           \
                       : line_launch<P, LINE_HPSI, true, FR>(s, a, nblocks, nt, lds, st))
 #define WVL_P(P)                                                                                 \
   return a.free == 3 ? WVL_F(P, 3)                                                               \
          : a.free == 2 ? WVL_F(P, 2)                                                             \
-         : mode == LINE_HPSI && !a.shared                                                        \
-             ? line_launch<P, LINE_HPSI, false, 0>(s, a, nblocks, nt, lds, st)                   \
-             : WVL_F(P, 0)
+         : a.shared ? WVL_F(P, 0)                                                                \
+         : mode == LINE_HPSI ? line_launch<P, LINE_HPSI, false, 0>(s, a, nblocks, nt, lds, st)   \
+                             : line_launch<P, LINE_HELM, false, 0>(s, a, nblocks, nt, lds, st)
   switch (prec) {
     case F64: WVL_P(F64);
     case F32: WVL_P(F32);
