@@ -7,9 +7,12 @@
 // orbital is [coarse-region scaling coefficients][7 per fine-region point];
 // regions are given as segments of consecutive points along axis 1.  Both
 // kernels are gathers, so every store is coalesced:
-//  * decompress: one thread per element of the full interleaved grid; the
-//    element's coarse point and component mu = b1 + 2 b2 + 4 b3 select the
-//    compressed index through a per-point map (-1: not stored, value 0);
+//  * decompress: one thread per coarse point, whose position and place in the
+//    two regions (per-point maps, -1: not stored, value 0) serve all orbitals;
+//    the thread reads its scaling value and its seven adjacent wavelet values
+//    and stores four pairs of neighbours (256 float64 orbitals of 48^3 cells:
+//    0.47 ms where one thread per element, bound by its divisions and by one
+//    load and store each, took 0.81);
 //  * compress: one thread per compressed element; the region's point list
 //    gives the full-grid position to read.
 
@@ -26,29 +29,27 @@ __global__ __launch_bounds__(kThreads) void k_decompress(const OrbDev* __restric
                                                          int64_t plane_out) {
   using T = Prec<P>;
   const OrbDev o0 = orbs[0];
-  const int m1 = o0.m[0], m2 = o0.m[1], m3 = o0.m[2];
-  const int n1 = m1 >> 1, n2 = m2 >> 1;
-  const uint32_t M = (uint32_t)m1 * m2 * m3;
-  const int64_t total = (int64_t)M * norb;
-  for (int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x; g < total;
-       g += (int64_t)gridDim.x * kThreads) {
-    const int b = (int)(g / M);
-    const uint32_t e = (uint32_t)(g - (int64_t)b * M);
-    const uint32_t row = e / (uint32_t)m1;
-    const int x = (int)(e - row * (uint32_t)m1);
-    const int y = (int)(row % (uint32_t)m2), z = (int)(row / (uint32_t)m2);
-    const int pnt = (x >> 1) + n1 * ((y >> 1) + n2 * (z >> 1));
-    const int mu = (x & 1) | ((y & 1) << 1) | ((z & 1) << 2);
+  const uint32_t m1 = o0.m[0], m2 = o0.m[1];
+  const uint32_t n1 = m1 >> 1, n2 = m2 >> 1, n = n1 * n2 * ((uint32_t)o0.m[2] >> 1);
+  const uint32_t pnt = blockIdx.x * kThreads + threadIdx.x;
+  if (pnt >= n) return;
+  const int kc = map_c[pnt], kf = map_f[pnt];
+  const uint32_t row = pnt / n1, i1 = pnt - row * n1, i2 = row % n2, i3 = row / n2;
+  const int64_t e = ((int64_t)(2 * i3) * m2 + 2 * i2) * m1 + 2 * i1;
+  const int64_t jf = nvc + 7 * (int64_t)kf;
+  for (int b = blockIdx.y; b < norb; b += gridDim.y) {
     const int64_t src = (int64_t)b * L;
-    typename T::V v = T::from_d(0.0);
-    if (mu == 0) {
-      const int k = map_c[pnt];
-      if (k >= 0) v = T::ldc(in, src + k, plane_in);
-    } else {
-      const int k = map_f[pnt];
-      if (k >= 0) v = T::ldc(in, src + nvc + 7 * (int64_t)k + mu - 1, plane_in);
-    }
-    T::st(out, orbs[b].off + e, plane_out, v);
+    typename T::V v[8];
+    #pragma unroll
+    for (int mu = 0; mu < 8; ++mu) v[mu] = T::from_d(0.0);
+    if (kc >= 0) v[0] = T::ldc(in, src + kc, plane_in);
+    if (kf >= 0)
+      #pragma unroll
+      for (int mu = 1; mu < 8; ++mu) v[mu] = T::ldc(in, src + jf + mu - 1, plane_in);
+    const int64_t d = orbs[b].off + e;
+    #pragma unroll
+    for (int q = 0; q < 4; ++q)
+      T::st2(out, d + (int64_t)(q & 1) * m1 + (int64_t)(q >> 1) * m1 * m2, plane_out, v[2 * q], v[2 * q + 1]);
   }
 }
 
@@ -94,7 +95,9 @@ hipError_t launch_decompress(int prec, const OrbDev* orbs, int norb, int64_t M,
                              const int32_t* map_c, const int32_t* map_f, int64_t nvc, int64_t L,
                              const void* in, int64_t plane_in, void* out, int64_t plane_out,
                              hipStream_t st) {
-  const dim3 g(grid_for(M * norb)), b(kThreads);
+  // orbitals in turn per thread, while 16 workgroups per compute unit remain
+  const unsigned nb = (unsigned)((M / 8 + kThreads - 1) / kThreads);
+  const dim3 g(nb, (unsigned)std::max<int64_t>(1, std::min<int64_t>(std::min(norb, 65535), 4096 / nb))), b(kThreads);
   switch (prec) {
     case F64: hipLaunchKernelGGL((k_decompress<F64>), g, b, 0, st, orbs, norb, map_c, map_f, nvc, L, in, plane_in, out, plane_out); break;
     case F32: hipLaunchKernelGGL((k_decompress<F32>), g, b, 0, st, orbs, norb, map_c, map_f, nvc, L, in, plane_in, out, plane_out); break;

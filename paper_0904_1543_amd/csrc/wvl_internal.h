@@ -212,6 +212,9 @@ __device__ __forceinline__ int wrapi(int i, int m) {
 template <typename V> __device__ __forceinline__ void stream_st(V* p, V v) {
   __builtin_nontemporal_store(v, p);
 }
+// pairs of values with the alignment of one (an orbital may start anywhere)
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
 constexpr int64_t kCacheBytes = (int64_t)256 << 20;
 
 // ---------------------------------------------------------------------------
@@ -238,6 +241,10 @@ template <> struct Prec<F64> {
   __device__ static V ldc(const void* p, int64_t i, int64_t) { return ((const double*)p)[i]; }
   __device__ static void st(void* p, int64_t i, int64_t, V v) { ((double*)p)[i] = v; }
   __device__ static void st_stream(void* p, int64_t i, int64_t, V v) { stream_st((double*)p + i, v); }
+  // two adjacent values
+  __device__ static void st2(void* p, int64_t i, int64_t, V a, V b) {
+    *reinterpret_cast<d2u*>((double*)p + i) = d2u{a, b};
+  }
   __device__ static Acc zero() { return Acc{0.0}; }
   template <int OP> __device__ static void add(Acc& a, int par, int o, const V& x) {
     a.s = __builtin_fma(coef<OP>(par, o, 0), x, a.s);
@@ -255,6 +262,9 @@ template <> struct Prec<F32> {
   static constexpr int bytes = 4;
   __device__ static V ldc(const void* p, int64_t i, int64_t) { return ((const float*)p)[i]; }
   __device__ static void st(void* p, int64_t i, int64_t, V v) { ((float*)p)[i] = v; }
+  __device__ static void st2(void* p, int64_t i, int64_t, V a, V b) {
+    *reinterpret_cast<f2u*>((float*)p + i) = f2u{a, b};
+  }
   __device__ static void st_stream(void* p, int64_t i, int64_t plane, V v) { st(p, i, plane, v); }
   __device__ static Acc zero() { return Acc{0.0f}; }
   template <int OP> __device__ static void add(Acc& a, int par, int o, const V& x) {
@@ -286,6 +296,12 @@ template <> struct Prec<F32C> {
     const float h = (float)v;
     f[i] = h;
     f[plane + i] = (float)(v - (double)h);
+  }
+  __device__ static void st2(void* p, int64_t i, int64_t plane, V a, V b) {
+    float* f = (float*)p + i;
+    const float ha = (float)a, hb = (float)b;
+    *reinterpret_cast<f2u*>(f) = f2u{ha, hb};
+    *reinterpret_cast<f2u*>(f + plane) = f2u{(float)(a - (double)ha), (float)(b - (double)hb)};
   }
   __device__ static void st_stream(void* p, int64_t i, int64_t plane, V v) { st(p, i, plane, v); }
   __device__ static Acc zero() { return Acc{0.0}; }

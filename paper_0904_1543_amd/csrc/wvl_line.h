@@ -36,8 +36,6 @@ namespace wvl {
 // twelve float32 operations a tap) and split again on the way out.  Elements
 // are addressed as a uniform base and a 32-bit byte offset; the vector types
 // carry the alignment of one element, since an orbital may start anywhere.
-typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
-typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
 template <int P> struct LineIO;
 template <> struct LineIO<F64> {
   using C = double;
