@@ -63,8 +63,7 @@ def stage_model(stage, prec, variant):
     operation count for the axes the stage covers."""
     es = ESIZE[prec]
     if stage == "xy_plane":
-        bound = "mfma" if variant == 3 else "alu"
-        return bound, 4 * es, 2 * FLOP_AXIS + FLOP_POINTWISE
+        return "alu", 4 * es, 2 * FLOP_AXIS + FLOP_POINTWISE
     if stage == "z_final":       # t, c, kxy in; H*psi out
         return "hbm", 4 * es, None
     if stage.endswith("_z") and stage.startswith(("ck", "cwt")) and variant >= 1:
