@@ -73,6 +73,7 @@ struct ZLineArgs {
   const void* t;         // ZL_FINAL
   const void* k0;        // nullable (not ZL_FINAL's): added
   const void* r;         // ZL_CG
+  void* x;               // ZL_CG, nullable: x += alpha times p of the step before
   void* out;
   void* pnew;            // ZL_CG
   const double* eps;
@@ -93,6 +94,10 @@ hipError_t launch_cg_alpha(int norb, const int32_t* pz, const int32_t* py, const
                            const int32_t* pr, const int32_t* ppre, const double* ez, const double* ey, const double* ex,
                            const double* prz, const double* ppp, const double* eps, void* sc,
                            hipStream_t st);
+// r -= alpha q alone (x is updated by ZL_CG, q holds the shift)
+hipError_t launch_cg_residual(int prec, const PassGeom& g, int ntiles, void* r, const void* q,
+                              const double* eps, const void* sc, int64_t plane, double* prz,
+                              double* prr, hipStream_t st);
 hipError_t launch_cg_update1(int prec, const PassGeom& g, int ntiles, void* x, void* r,
                              const void* p, const void* q, const double* eps, int shift,
                              const void* sc, int64_t plane, double* prz, double* prr,
@@ -172,6 +177,7 @@ struct XyArgs {
   int32_t free;          // plane kernel: isolated axes (1: axis 1, 2: axis 2; 0, 2 or 3)
   int32_t m3_rs;         // ... planes of u and t per orbital, in arrays of plane stride plane_u
   int64_t plane_u;
+  const double* eps;     // HELM: kq - eps_b p (nullable: kq)
   const void* u;
   const void* c;
   void* t;

@@ -566,6 +566,10 @@ struct LineKernel {
           put(B, i, rc[i]);
           wave_sync();
           kinetic<1>(B, i, (C)o.ks1, kx[i], ek);
+          if (MODE == LINE_HELM && a.eps) {   // p is still in B
+            const C ep = (C)((const __attribute__((address_space(4))) double*)a.eps)[b];
+            each<OP_CK, 1>(i, [&](int u, int pos, int, int) { kx[i][u] -= ep * B[pos]; });
+          }
         }
       }
       if (MODE == LINE_HELM) {   // kq and the next plane arrive behind the columns

@@ -11,7 +11,7 @@
 //
 // Bound by memory traffic: 256 orbitals of 48^3 cells take, in float64, 0.65 ms
 // for W (5.6 TB/s), 1.41 for the last step (5.1) and 1.31 for the direction
-// update with K (5.5); in float pairs 0.75 and 1.49.  The strided passes (0.71,
+// update with K (5.5; with the update of x 2.07, 5.2); in float pairs 0.75 and 1.49.  The strided passes (0.71,
 // 1.77, 1.53; 0.83 and 2.39), whose lanes hold a window of the line, read its
 // first 58 values twice, spend a third of their vector instructions on moving
 // the window and fill the registers with it; they stay for longer lines than
@@ -135,6 +135,19 @@ struct ZLine {
     if (MODE == ZL_CG) {
       C po[NR];
       load(a.in, po);
+      if (a.x) {
+        load(a.x, r);
+        const double al = a.sc[b].alpha;
+        uint32_t o = w * L + xr;
+        char* d = IO::at(a.x, off);
+        #pragma unroll
+        for (int n = 0; n < NR; ++n, o += 4 * L)
+          if (onr && 4 * n + w < m) {
+            const C v = (C)((double)r[n] + al * (double)po[n]);
+            if (P == F64 && g.stream) IO::st(d, o, a.plane, v);
+            else IO::st_keep(d, o, a.plane, v);
+          }
+      }
       if (a.r) {
         load(a.r, r);
         // 1 / diag at this lane's parities (rows 4 n + w: w's parity)

@@ -10,7 +10,9 @@
 //   update1  x += alpha p, r -= alpha q, z = r / diag
 //   beta     per orbital: beta = (r.z)_new / (r.z)_old
 //   update2  p = z + beta p (on the periodic combined-filter forms inside the
-//            next z pass: wvl_passes_impl.h)
+//            next z pass, wvl_line_z.h and wvl_passes_impl.h; with the plane
+//            kernel that z pass also does x += alpha p, the operator takes the
+//            shift, and update1 is r -= alpha q alone until the last step)
 // The Jacobi preconditioner diag is the diagonal of the operator in the
 // wavelet basis: per axis one value for scaling and one for wavelet
 // coefficients (OrbDev::kdiag), minus eps.  Every element kernel reads and
@@ -274,6 +276,55 @@ __global__ __launch_bounds__(kThreads) void k_cg_update1(PassGeom g, void* x, vo
   block_sum_store(rr, prr + blockIdx.x);
 }
 
+// r -= alpha q; partials of r.z, r.r
+template <int P>
+__global__ __launch_bounds__(kThreads) void k_cg_residual(PassGeom g, void* r, const void* q,
+                                                          const double* __restrict__ eps,
+                                                          const CgScal* __restrict__ sc,
+                                                          int64_t plane, double* prz, double* prr) {
+  using L = G4<P>;
+  int b, t;
+  find_tile(g.prefix, g.norb, blockIdx.x, b, t);
+  const OrbDev od = g.orbs[b];
+  const uint32_t M = (uint32_t)od.m[0] * od.m[1] * od.m[2];
+  const uint32_t e0 = (uint32_t)t * kCgTile + 4 * threadIdx.x;
+  const double a = sc[b].alpha;
+  const CgInv inv(od, eps[b]);
+  double rz = 0.0, rr = 0.0;
+  CgPos pos(od, e0, kCgStep);
+  #pragma unroll 1
+  for (int ch = 0; ch < kCgChunks; ++ch) {
+    const uint32_t c0 = e0 + (uint32_t)(ch * kCgG) * kCgStep;
+    double qv[kCgG][4], rv[kCgG][4];
+    #pragma unroll
+    for (int k = 0; k < kCgG; ++k) {
+      const uint32_t e = c0 + (uint32_t)k * kCgStep;
+      if (e < M) {
+        L::ld(q, od.off + e, plane, qv[k]);
+        L::ld(r, od.off + e, plane, rv[k]);
+      }
+    }
+    #pragma unroll
+    for (int k = 0; k < kCgG; ++k) {
+      const uint32_t e = c0 + (uint32_t)k * kCgStep;
+      if (e < M) {
+        double w[4], rn[4];
+        inv.group(pos, w);
+        #pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          rn[j] = rv[k][j] - a * qv[k][j];
+          rz += rn[j] * (rn[j] * w[j]);
+          rr += rn[j] * rn[j];
+        }
+        L::st(r, od.off + e, plane, rn);
+      }
+      pos.next();
+    }
+  }
+  block_sum_store(rz, prz + blockIdx.x);
+  block_sum_store(rr, prr + blockIdx.x);
+}
+
 __global__ __launch_bounds__(kThreads) void k_cg_beta(const int32_t* pp, const double* prz,
                                                       CgScal* sc) {
   const int b = blockIdx.x;
@@ -394,6 +445,15 @@ hipError_t launch_cg_update1(int prec, const PassGeom& g, int ntiles, void* x, v
                              hipStream_t st) {
   if (ntiles == 0) return hipSuccess;
   WVL_PREC_SWITCH(prec, k_cg_update1, dim3(ntiles), dim3(kThreads), 0, st, g, x, r, p, q, eps, shift,
+                  (const CgScal*)sc, plane, prz, prr);
+  return hipGetLastError();
+}
+
+hipError_t launch_cg_residual(int prec, const PassGeom& g, int ntiles, void* r, const void* q,
+                              const double* eps, const void* sc, int64_t plane, double* prz,
+                              double* prr, hipStream_t st) {
+  if (ntiles == 0) return hipSuccess;
+  WVL_PREC_SWITCH(prec, k_cg_residual, dim3(ntiles), dim3(kThreads), 0, st, g, r, q, eps,
                   (const CgScal*)sc, plane, prz, prr);
   return hipGetLastError();
 }
