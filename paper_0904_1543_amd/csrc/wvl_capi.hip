@@ -1683,8 +1683,10 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
   const bool fused = !p->bc_any && !separate && !exact;
   // ... which then also updates x, the plane kernel applying the shift: a step
   // moves 12 batch arrays instead of 13 (5 steps on 256 float64 orbitals of 48^3
-  // cells: 25.8 ms -> 24.6; per step x and r 2.05 -> 1.02, z pass 1.31 -> 2.07)
-  const bool lite = fused && plane_form && use_line(p) && !p->zl.empty();
+  // cells: 25.8 ms -> 24.6; per step x and r 2.05 -> 1.02, z pass 1.31 -> 2.07).
+  // Not in plain float32, where the plane kernel computes in float32: the CG
+  // updates form q - eps p in float64 with the float64 eps.
+  const bool lite = fused && plane_form && use_line(p) && !p->zl.empty() && p->prec != WVL_F32;
   const int32_t* ppre = p->d_pc;   // tiles of the partials of p.p
   auto z_pass = [&](int it) {
     if (it == 0) return q.pass(OP_CK, 3, Pv, Q, nullptr, 1.0, ez);

@@ -177,7 +177,7 @@ struct XyArgs {
   int32_t free;          // plane kernel: isolated axes (1: axis 1, 2: axis 2; 0, 2 or 3)
   int32_t m3_rs;         // ... planes of u and t per orbital, in arrays of plane stride plane_u
   int64_t plane_u;
-  const double* eps;     // HELM: kq - eps_b p (nullable: kq)
+  const double* eps;     // HELM, not F32: kq - eps_b p (nullable: kq)
   const void* u;
   const void* c;
   void* t;

@@ -566,7 +566,7 @@ struct LineKernel {
           put(B, i, rc[i]);
           wave_sync();
           kinetic<1>(B, i, (C)o.ks1, kx[i], ek);
-          if (MODE == LINE_HELM && a.eps) {   // p is still in B
+          if (MODE == LINE_HELM && P != F32 && a.eps) {   // p is still in B
             const C ep = (C)((const __attribute__((address_space(4))) double*)a.eps)[b];
             each<OP_CK, 1>(i, [&](int u, int pos, int, int) { kx[i][u] -= ep * B[pos]; });
           }

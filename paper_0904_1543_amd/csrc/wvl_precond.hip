@@ -11,8 +11,9 @@
 //   beta     per orbital: beta = (r.z)_new / (r.z)_old
 //   update2  p = z + beta p (on the periodic combined-filter forms inside the
 //            next z pass, wvl_line_z.h and wvl_passes_impl.h; with the plane
-//            kernel that z pass also does x += alpha p, the operator takes the
-//            shift, and update1 is r -= alpha q alone until the last step)
+//            kernel, which computes float64 values and float pairs in float64,
+//            that z pass also does x += alpha p, the operator takes the shift,
+//            and update1 is r -= alpha q alone until the last step)
 // The Jacobi preconditioner diag is the diagonal of the operator in the
 // wavelet basis: per axis one value for scaling and one for wavelet
 // coefficients (OrbDev::kdiag), minus eps.  Every element kernel reads and
