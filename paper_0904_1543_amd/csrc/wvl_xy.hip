@@ -8,12 +8,12 @@
 namespace wvl {
 
 template <int P, bool SH>
-void xy_launch_v(const XyArgs& a, int nblocks, size_t lds, hipStream_t st);
+void xy_launch_v(const XyArgs& a, int mi, int nblocks, size_t lds, hipStream_t st);
 template <bool SH>
-void xy_launch_m(const XyArgs& a, int nblocks, size_t lds, hipStream_t st);
+void xy_launch_m(const XyArgs& a, int mt, int nblocks, size_t lds, hipStream_t st);
 template <int P>
-void helm_launch_v(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st);
-void helm_launch_mf(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st);
+void helm_launch_v(const HelmArgs& a, int mi, int nblocks, size_t lds, hipStream_t st);
+void helm_launch_mf(const HelmArgs& a, int mt, int nblocks, size_t lds, hipStream_t st);
 
 template <int P, int MODE, bool SH, int FREE>
 hipError_t line_launch(int shape, const XyArgs& a, int nblocks, int nt, size_t lds, hipStream_t st);
@@ -63,13 +63,15 @@ hipError_t launch_xy(int prec, const XyArgs& a, int m1, int m2, int nblocks, hip
   if (mx && !xy_matrix_engine(prec, m1, m2)) return hipErrorInvalidValue;
   const size_t lds = xy_lds_bytes(prec, m1, m2, mx);
   if (mx) {
-    sh ? xy_launch_m<true>(a, nblocks, lds, st) : xy_launch_m<false>(a, nblocks, lds, st);
+    const int mt = xy_tiles(m1, m2);
+    sh ? xy_launch_m<true>(a, mt, nblocks, lds, st) : xy_launch_m<false>(a, mt, nblocks, lds, st);
     return hipGetLastError();
   }
+  const int mi = xy_items(m1, m2);
   switch (prec) {
-    case F64: sh ? xy_launch_v<F64, true>(a, nblocks, lds, st) : xy_launch_v<F64, false>(a, nblocks, lds, st); break;
-    case F32: sh ? xy_launch_v<F32, true>(a, nblocks, lds, st) : xy_launch_v<F32, false>(a, nblocks, lds, st); break;
-    default:  sh ? xy_launch_v<F32C, true>(a, nblocks, lds, st) : xy_launch_v<F32C, false>(a, nblocks, lds, st); break;
+    case F64: sh ? xy_launch_v<F64, true>(a, mi, nblocks, lds, st) : xy_launch_v<F64, false>(a, mi, nblocks, lds, st); break;
+    case F32: sh ? xy_launch_v<F32, true>(a, mi, nblocks, lds, st) : xy_launch_v<F32, false>(a, mi, nblocks, lds, st); break;
+    default:  sh ? xy_launch_v<F32C, true>(a, mi, nblocks, lds, st) : xy_launch_v<F32C, false>(a, mi, nblocks, lds, st); break;
   }
   return hipGetLastError();
 }
@@ -80,13 +82,14 @@ hipError_t launch_helm_xy(int prec, const HelmArgs& a, int m1, int m2, int nbloc
   if (engine && !xy_matrix_engine(prec, m1, m2)) return hipErrorInvalidValue;
   const size_t lds = xy_lds_bytes(prec, m1, m2, engine);
   if (engine) {
-    helm_launch_mf(a, nblocks, lds, st);
+    helm_launch_mf(a, xy_tiles(m1, m2), nblocks, lds, st);
     return hipGetLastError();
   }
+  const int mi = xy_items(m1, m2);
   switch (prec) {
-    case F64: helm_launch_v<F64>(a, nblocks, lds, st); break;
-    case F32: helm_launch_v<F32>(a, nblocks, lds, st); break;
-    default:  helm_launch_v<F32C>(a, nblocks, lds, st); break;
+    case F64: helm_launch_v<F64>(a, mi, nblocks, lds, st); break;
+    case F32: helm_launch_v<F32>(a, mi, nblocks, lds, st); break;
+    default:  helm_launch_v<F32C>(a, mi, nblocks, lds, st); break;
   }
   return hipGetLastError();
 }

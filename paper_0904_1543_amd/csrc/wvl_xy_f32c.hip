@@ -2,7 +2,7 @@
 #include "wvl_xy_impl.h"
 
 namespace wvl {
-template void xy_launch_v<F32C, true>(const XyArgs&, int, size_t, hipStream_t);
-template void xy_launch_v<F32C, false>(const XyArgs&, int, size_t, hipStream_t);
-template void helm_launch_v<F32C>(const HelmArgs&, int, size_t, hipStream_t);
+template void xy_launch_v<F32C, true>(const XyArgs&, int, int, size_t, hipStream_t);
+template void xy_launch_v<F32C, false>(const XyArgs&, int, int, size_t, hipStream_t);
+template void helm_launch_v<F32C>(const HelmArgs&, int, int, size_t, hipStream_t);
 }  // namespace wvl

@@ -629,23 +629,40 @@ void k_helm_xy(HelmArgs a) {
   if (threadIdx.x == 0) a.ekin[blockIdx.x] = sk;
 }
 
+// Instances by the work items (vector) or tiles (matrix) of a thread or wave:
+// results of a pass stay in registers, so the largest instance spills what a
+// smaller plane does not need (32 orbitals of 256 x 16 x 32 points, one potential
+// each: H*psi in float32 371 us with the largest for all and 142 with these, in
+// float64 224 and 156).
 template <int P, bool SH>
-void xy_launch_v(const XyArgs& a, int nblocks, size_t lds, hipStream_t st) {
-  hipLaunchKernelGGL((k_xy<P, VecEngine<P, kMaxItems>, SH>), dim3(nblocks), dim3(kXyThreads), lds, st, a);
+void xy_launch_v(const XyArgs& a, int mi, int nblocks, size_t lds, hipStream_t st) {
+  const dim3 g(nblocks), b(kXyThreads);
+  if (mi <= 3) hipLaunchKernelGGL((k_xy<P, VecEngine<P, 3>, SH>), g, b, lds, st, a);
+  else if (mi <= 5) hipLaunchKernelGGL((k_xy<P, VecEngine<P, 5>, SH>), g, b, lds, st, a);
+  else hipLaunchKernelGGL((k_xy<P, VecEngine<P, kMaxItems>, SH>), g, b, lds, st, a);
 }
 
 template <bool SH>
-void xy_launch_m(const XyArgs& a, int nblocks, size_t lds, hipStream_t st) {
-  hipLaunchKernelGGL((k_xy<F64, MfEngine<8>, SH>), dim3(nblocks), dim3(kXyThreads), lds, st, a);
+void xy_launch_m(const XyArgs& a, int mt, int nblocks, size_t lds, hipStream_t st) {
+  const dim3 g(nblocks), b(kXyThreads);
+  if (mt <= 2) hipLaunchKernelGGL((k_xy<F64, MfEngine<2>, SH>), g, b, lds, st, a);
+  else if (mt <= 5) hipLaunchKernelGGL((k_xy<F64, MfEngine<5>, SH>), g, b, lds, st, a);
+  else hipLaunchKernelGGL((k_xy<F64, MfEngine<8>, SH>), g, b, lds, st, a);
 }
 
 template <int P>
-void helm_launch_v(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st) {
-  hipLaunchKernelGGL((k_helm_xy<P, VecEngine<P, kMaxItems>>), dim3(nblocks), dim3(kXyThreads), lds, st, a);
+void helm_launch_v(const HelmArgs& a, int mi, int nblocks, size_t lds, hipStream_t st) {
+  const dim3 g(nblocks), b(kXyThreads);
+  if (mi <= 3) hipLaunchKernelGGL((k_helm_xy<P, VecEngine<P, 3>>), g, b, lds, st, a);
+  else if (mi <= 5) hipLaunchKernelGGL((k_helm_xy<P, VecEngine<P, 5>>), g, b, lds, st, a);
+  else hipLaunchKernelGGL((k_helm_xy<P, VecEngine<P, kMaxItems>>), g, b, lds, st, a);
 }
 
-inline void helm_launch_m(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st) {
-  hipLaunchKernelGGL((k_helm_xy<F64, MfEngine<8>>), dim3(nblocks), dim3(kXyThreads), lds, st, a);
+inline void helm_launch_m(const HelmArgs& a, int mt, int nblocks, size_t lds, hipStream_t st) {
+  const dim3 g(nblocks), b(kXyThreads);
+  if (mt <= 2) hipLaunchKernelGGL((k_helm_xy<F64, MfEngine<2>>), g, b, lds, st, a);
+  else if (mt <= 5) hipLaunchKernelGGL((k_helm_xy<F64, MfEngine<5>>), g, b, lds, st, a);
+  else hipLaunchKernelGGL((k_helm_xy<F64, MfEngine<8>>), g, b, lds, st, a);
 }
 
 }  // namespace wvl

@@ -2,9 +2,9 @@
 #include "wvl_xy_impl.h"
 
 namespace wvl {
-template void xy_launch_m<true>(const XyArgs&, int, size_t, hipStream_t);
-template void xy_launch_m<false>(const XyArgs&, int, size_t, hipStream_t);
-void helm_launch_mf(const HelmArgs& a, int nblocks, size_t lds, hipStream_t st) {
-  helm_launch_m(a, nblocks, lds, st);
+template void xy_launch_m<true>(const XyArgs&, int, int, size_t, hipStream_t);
+template void xy_launch_m<false>(const XyArgs&, int, int, size_t, hipStream_t);
+void helm_launch_mf(const HelmArgs& a, int mt, int nblocks, size_t lds, hipStream_t st) {
+  helm_launch_m(a, mt, nblocks, lds, st);
 }
 }  // namespace wvl
