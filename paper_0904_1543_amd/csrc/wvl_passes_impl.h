@@ -56,6 +56,20 @@ __device__ __forceinline__ int64_t z_segment(int t, int64_t L, int m, int zlen, 
   return (int64_t)(t - seg * blocks) * kThreads + threadIdx.x;
 }
 
+// N values of a periodic line of m from position i0 on, into f(i, position):
+// one division for the first position, the others stepped.  With a division for
+// each of the up to 88 loads of a first window the last z step of 64 float32
+// orbitals of 144 x 20 x 8 points took 28.3 us, now 18.1.
+template <int N, typename F>
+__device__ __forceinline__ void wrap_run(int i0, int m, F&& f) {
+  int s = wrapi(i0, m);
+  #pragma unroll
+  for (int i = 0; i < N; ++i) {
+    f(i, s);
+    s = s + 1 == m ? 0 : s + 1;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Strided-axis pass (AXIS = 2 or 3)
 // ---------------------------------------------------------------------------
@@ -87,9 +101,7 @@ __global__ __launch_bounds__(kThreads) void k_strided(PassGeom g, const void* __
         od.off + (AXIS == 3 ? line : (line / m1) * ((int64_t)m1 * m2) + (line % m1));
     const double ks = AXIS == 3 ? od.kscale[2] : od.kscale[1];
     V win[W + 1];
-    #pragma unroll
-    for (int i = 0; i < W - 1; ++i)
-      win[i] = T::ldc(in, base + (int64_t)wrapi(k0l + i - OHI, m) * stride, plane);
+    wrap_run<W - 1>(k0l - OHI, m, [&](int i, int s) { win[i] = T::ldc(in, base + (int64_t)s * stride, plane); });
     // The loads of the next kPf output pairs are in flight while a pair is
     // computed (ring of registers, refilled as it is consumed): a wave keeps
     // 2 kPf input loads (and as many accumulator loads) outstanding.
@@ -187,10 +199,8 @@ __global__ __launch_bounds__(kThreads) void k_zfinal(PassGeom g, const void* __r
     const double ks = od.kscale[2];
     auto at = [&](int i) { return base + (int64_t)wrapi(i, m) * stride; };
     V wt[WT + 1], wk[WK + 1];
-    #pragma unroll
-    for (int i = 0; i < WT - 1; ++i) wt[i] = T::ldc(t, at(k0l + i - HT), plane);
-    #pragma unroll
-    for (int i = 0; i < WK - 1; ++i) wk[i] = T::ldc(c, at(k0l + i - HK), plane);
+    wrap_run<WT - 1>(k0l - HT, m, [&](int i, int s) { wt[i] = T::ldc(t, base + (int64_t)s * stride, plane); });
+    wrap_run<WK - 1>(k0l - HK, m, [&](int i, int s) { wk[i] = T::ldc(c, base + (int64_t)s * stride, plane); });
     V qt0[kPfZ], qt1[kPfZ], qk0[kPfZ], qk1[kPfZ], a0[kPfZ], a1[kPfZ];
     auto fetch = [&](int d, int kk) {
       qt0[d] = T::ldc(t, at(kk - LT), plane);
@@ -288,12 +298,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_cg_z(PassGeom g, const void* __
     #pragma unroll
     for (int i0 = 0; i0 < W - 1; i0 += FB) {
       V rv[FB], pv[FB];
-      #pragma unroll
-      for (int j = 0; j < FB; ++j)
+      wrap_run<FB>(k0l + i0 - OHI, m, [&](int j, int z) {
         if (i0 + j < W - 1) {
-          rv[j] = T::ldc(r, at(k0l + i0 + j - OHI), plane);
-          pv[j] = T::ldc(pold, at(k0l + i0 + j - OHI), plane);
+          rv[j] = T::ldc(r, base + (int64_t)z * L, plane);
+          pv[j] = T::ldc(pold, base + (int64_t)z * L, plane);
         }
+      });
       #pragma unroll
       for (int j = 0; j < FB; ++j)
         if (i0 + j < W - 1) win[i0 + j] = dir(rv[j], pv[j], (i0 + j - OHI) & 1);
