@@ -473,16 +473,16 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
       return fail(WVL_EINVAL, "too many tiles");
     }
   }
-  // z passes with whole lines in LDS: for lines that have a shape, in orbitals
-  // that 32-bit byte offsets reach; any size of batch (one orbital of 16^3
-  // cells: 10 + 15 us -> 5 + 9)
+  // z passes with whole lines in LDS: for lines that have a shape (of one length:
+  // where they pay), in orbitals that 32-bit byte offsets reach; any size of batch
   p->pl.assign(norb + 1, 0);
   if (!p->bc_any) {
     bool ok = true;
     int64_t tiles = 0;
     for (const OrbDev& d : p->orbs) {
       tiles += ((int64_t)d.m[0] * d.m[1] + 15) / 16 + kZWaves;
-      ok = ok && (int64_t)d.m[0] * d.m[1] * d.m[2] < (int64_t)1 << 28 && line_z_shape(d.m[2]) >= 0;
+      ok = ok && (int64_t)d.m[0] * d.m[1] * d.m[2] < (int64_t)1 << 28 &&
+           (uniform ? line_z_pays(prec, d.m[2]) : line_z_shape(d.m[2]) >= 0);
     }
     ok = ok && tiles < (int64_t)1 << 30;
     for (int b = 0; b < norb; ++b) {

@@ -15,7 +15,8 @@
 // 1.77, 1.53; 0.83 and 2.39), whose lanes hold a window of the line, read its
 // first 58 values twice, spend a third of their vector instructions on moving
 // the window and fill the registers with it; they stay for longer lines than
-// the LDS holds a workgroup's worth of.  Work queues are not used: a queue's
+// the LDS holds a workgroup's worth of, and for the lengths at which they are
+// faster (line_z_pays).  Work queues are not used: a queue's
 // barriers and its counter cost 12% of the last step.
 #pragma once
 
