@@ -1659,6 +1659,8 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
   const bool helm_mx = xy_matrix_engine(p->prec, p->xy_m1, p->xy_m2) && !getenv("WVL_XY_VECTOR");
   const int form = precond_form(p, mode);
   const bool exact = form == 2 && p->oz_pc, plane_form = form != 0 && !exact;
+  const bool helm_line = use_line(p) &&
+                         (p->M > 0 || !helm_whole(p->prec, p->xy_m1, p->xy_m2, p->pq[p->norb]));
   double* kpl = plane_form || exact ? (double*)wsp(ws, p->o_kpl) : nullptr;
   OzHelmArgs oa{};
   if (exact) {
@@ -1686,7 +1688,7 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
   // cells: 25.8 ms -> 24.6; per step x and r 2.05 -> 1.02, z pass 1.31 -> 2.07).
   // Not in plain float32, where the plane kernel computes in float32: the CG
   // updates form q - eps p in float64 with the float64 eps.
-  const bool lite = fused && plane_form && use_line(p) && !p->zl.empty() && p->prec != WVL_F32;
+  const bool lite = fused && plane_form && helm_line && !p->zl.empty() && p->prec != WVL_F32;
   const int32_t* ppre = p->d_pc;   // tiles of the partials of p.p
   auto z_pass = [&](int it) {
     if (it == 0) return q.pass(OP_CK, 3, Pv, Q, nullptr, 1.0, ez);
@@ -1730,7 +1732,7 @@ int wvl_precondition(wvl_plan* p, const void* g, const double* eps, int32_t iter
       // K_z p by the z pass, then (K_x + K_y) p added plane by plane
       WVL_CHK(z_pass(it));
       Mark mk(p, st, ST_HELM);
-      if (use_line(p)) {
+      if (helm_line) {
         XyArgs xa = xy_args(p, ws);
         xa.c = Pv;
         xa.kxy = Q;

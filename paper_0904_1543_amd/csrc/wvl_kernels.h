@@ -213,6 +213,8 @@ struct HelmArgs {
 hipError_t launch_helm_xy(int prec, const HelmArgs& a, int m1, int m2, int nblocks, bool engine,
                           hipStream_t st);
 
+// whether a batch of several grids takes launch_helm_xy rather than launch_line
+bool helm_whole(int prec, int m1, int m2, int nplanes);
 // engine: the float64 matrix-core form of the in-plane passes
 bool xy_matrix_engine(int prec, int m1, int m2);
 // Exact-product engine of the compensated form (wvl_oz.hip): uniform batches

@@ -46,6 +46,23 @@ bool xy_matrix_engine(int prec, int m1, int m2) {
   return prec == F64 && xy_tiles(m1, m2) <= 8 && (size_t)m2 * mf_pitch(m1) * 8 <= 160 * 1024;
 }
 
+// The preconditioner's operator over a batch of several grids, planes of up to
+// m1 x m2 values: whether one launch of the workgroup-wide kernel is faster than
+// the plane kernel, which takes a launch for each of its shapes, sized for the
+// class's largest plane, with one plane a workgroup (no second one to load
+// ahead).  Three CG steps on 32 / 100 orbitals of 8..48 cells an axis, plane
+// kernel against this: float64 618 / 2063 us against 545 / 1984, float32 515 /
+// 1454 against 427 / 1266.  Planes of up to 64 x 64 have few shapes (8..24 cells,
+// 100 orbitals, 464 and 463 us; 378 and 387); larger ones than 96 x 96 spill the
+// instances here (16..64 cells, 100 orbitals: 5.1 and 6.0 ms; 3.4 and 8.6), which
+// in float64, up to 112 x 112, a batch of few planes does not notice (8..52 cells,
+// 32 orbitals 896 and 812 us, 100 orbitals 2498 and 2800).
+bool helm_whole(int prec, int m1, int m2, int nplanes) {
+  if (prec == F32C || std::max(m1, m2) <= 64) return false;
+  if (prec == F32) return xy_supported(prec, m1, m2, false) && xy_items(m1, m2) <= 5;
+  return xy_matrix_engine(prec, m1, m2) && xy_tiles(m1, m2) <= (nplanes <= 2048 ? 7 : 5);
+}
+
 size_t xy_lds_bytes(int prec, int m1, int m2, bool engine) {
   if (engine) return (size_t)m2 * mf_pitch(m1) * 8;
   return (size_t)m2 * (m1 + 1) * (prec == F32 ? 4 : 8);
