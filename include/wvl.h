@@ -309,15 +309,18 @@ int wvl_plan_sync(wvl_plan *plan, void *stream);
  * WVL_AUTOTUNE the environment variable WVL_NO_PLANE_KERNEL forces 0,
  * WVL_F32C_VECTOR keeps WVL_F32C off variant 3 and WVL_XY_VECTOR forces 1
  * over 2 (the workgroup-wide kernel with vector FMA); WVL_PLANE_OCCUPANCY=2
- * runs the workgroup-wide kernel in every precision,
+ * runs the workgroup-wide kernel in every precision, compiled for 2 instead of
+ * 4 waves per SIMD (where the float64 matrix-core form then keeps its density
+ * group's plane in LDS; WVL_NO_RHO_LDS keeps it in memory),
  * WVL_EXACT_OCCUPANCY_Z=2 the last z kernel of the digit products for 2, and
  * WVL_NO_ZFUSE runs the last z step as two passes instead of one fused
  * launch (same results bit for bit; the fused launch is used for WVL_F64,
  * WVL_F32 and variant 3).)  With WVL_AUTOTUNE, times_ms[k] (k < ntimes, at most 15
  * candidates) receives the mean time of candidate k = 3 seq + shape, or -1
  * where it was not available:
- *   seq 0 one pass per axis; 1 the plane kernel; 2 the workgroup-wide plane
- *   kernel; 3 the same with vector FMA (WVL_F64 only); 4 variant 3;
+ *   seq 0 one pass per axis; 1 the plane kernel (workgroup-wide at 4 waves per
+ *   SIMD for planes too long for it); 2 the workgroup-wide kernel at 2 waves per
+ *   SIMD; 3 the same at 4 with vector FMA (WVL_F64 only); 4 variant 3;
  *   shape 0 default tiles; 1 axis-1 tiles of half as many rows (seq 0 only);
  *   2 persistent launches of 4 instead of 8 workgroups per CU (WVL_PERSISTENT
  *   plans only).

@@ -1159,6 +1159,7 @@ XyArgs xy_args(const wvl_plan* p, void* ws) {
   a.epot = (double*)wsp(ws, p->o_epl);
   a.ekin = (double*)wsp(ws, p->o_kpl);
   a.engine = p->xy_engine;
+  a.occupancy = p->xy_occ;
   if (p->bc_any) {
     a.M = p->Mrs;
     a.free = bc_line_axes(p);
@@ -1262,7 +1263,7 @@ int hpsi_sequence(wvl_plan* p, hipStream_t st, const void* c, const double* V, d
         xa.queue = q.queue++;
         const size_t lds = xy_lds_bytes(p->prec, p->xy_m1, p->xy_m2, p->xy_engine != 0);
         nblocks = std::min(nblocks, std::max(1, p->ctx->cus) *
-                                        std::max(1, std::min(2, (int)(p->ctx->lds_per_block / lds))));
+                                        std::max(1, std::min(p->xy_occ / 2, (int)(p->ctx->lds_per_block / lds))));
       }
       Mark mk(p, st, ST_XY);
       WVL_CHK(launch_xy(p->prec, xa, p->xy_m1, p->xy_m2, nblocks, st));
@@ -1327,10 +1328,11 @@ int hpsi_sequence(wvl_plan* p, hipStream_t st, const void* c, const double* V, d
 // Launch candidates of wvl_local_hpsi, timed on the plan's own batch (zero
 // data: no kernel's work depends on values).  Candidate k = 3 * seq + shape:
 //   seq 0: one 1D pass per axis and operator;
-//   seq 1: plane-resident kernel;
-//   seq 2: workgroup-wide plane kernel (occ 2), default engine;
-//   seq 3: the same with the vector FMA engine (float64 only, where the
-//          matrix-core engine is the default);
+//   seq 1: plane-resident kernel (planes with a shape of the plane kernel;
+//          others the workgroup-wide one at 4 waves per SIMD);
+//   seq 2: workgroup-wide kernel at 2 waves per SIMD, default engine;
+//   seq 3: workgroup-wide kernel at 4 with the vector FMA engine (float64
+//          only, where the matrix-core engine is the default);
 //   shape 0: default tiles (axis-1 tiles as many rows as fit in LDS;
 //            persistent launches of 8 workgroups per CU);
 //   shape 1: axis-1 tiles of half as many rows (seq 0 only: the other

@@ -190,6 +190,9 @@ struct XyArgs {
   double* epot;          // per (orbital, plane)
   double* ekin;          // per (orbital, plane): <c, (K_x + K_y) c> over the plane
   int32_t engine;        // workgroup-wide kernel: 0 vector FMA passes, 1 float64 matrix-core passes
+  int32_t occupancy;     // ... waves per SIMD it is compiled for (2 or 4)
+  int32_t rho_lds;       // ... shared, matrix engine, 2 waves per SIMD: the group's
+                         // density plane kept in LDS (set by launch_xy)
   int32_t slot;          // shared, vector engine: orbital g * G + slot of every group g
   // persistent launch of the unshared path (queue != nullptr): planes taken
   // from the queue in the order of `order` (prefix of planes over perm)
