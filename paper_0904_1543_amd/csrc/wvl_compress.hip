@@ -39,17 +39,15 @@ __global__ __launch_bounds__(kThreads) void k_decompress(const OrbDev* __restric
   const int64_t jf = nvc + 7 * (int64_t)kf;
   for (int b = blockIdx.y; b < norb; b += gridDim.y) {
     const int64_t src = (int64_t)b * L;
-    typename T::V v[8];
-    #pragma unroll
-    for (int mu = 0; mu < 8; ++mu) v[mu] = T::from_d(0.0);
-    if (kc >= 0) v[0] = T::ldc(in, src + kc, plane_in);
+    typename T::W v[8] = {};
+    if (kc >= 0) v[0] = T::ldw(in, src + kc, plane_in);
     if (kf >= 0)
       #pragma unroll
-      for (int mu = 1; mu < 8; ++mu) v[mu] = T::ldc(in, src + jf + mu - 1, plane_in);
+      for (int mu = 1; mu < 8; ++mu) v[mu] = T::ldw(in, src + jf + mu - 1, plane_in);
     const int64_t d = orbs[b].off + e;
     #pragma unroll
     for (int q = 0; q < 4; ++q)
-      T::st2(out, d + (int64_t)(q & 1) * m1 + (int64_t)(q >> 1) * m1 * m2, plane_out, v[2 * q], v[2 * q + 1]);
+      T::stw2(out, d + (int64_t)(q & 1) * m1 + (int64_t)(q >> 1) * m1 * m2, plane_out, v[2 * q], v[2 * q + 1]);
   }
 }
 
@@ -82,7 +80,7 @@ __global__ __launch_bounds__(kThreads) void k_compress(const OrbDev* __restrict_
     const int i2 = r % n2, i3 = r / n2;
     const int64_t e = ((int64_t)(2 * i3 + ((mu >> 2) & 1)) * m2 + (2 * i2 + ((mu >> 1) & 1))) * m1 +
                       2 * i1 + (mu & 1);
-    T::st(out, g, plane_out, T::ldc(in, orbs[b].off + e, plane_in));
+    T::stw(out, g, plane_out, T::ldw(in, orbs[b].off + e, plane_in));
   }
 }
 

@@ -241,8 +241,11 @@ template <> struct Prec<F64> {
   __device__ static V ldc(const void* p, int64_t i, int64_t) { return ((const double*)p)[i]; }
   __device__ static void st(void* p, int64_t i, int64_t, V v) { ((double*)p)[i] = v; }
   __device__ static void st_stream(void* p, int64_t i, int64_t, V v) { stream_st((double*)p + i, v); }
-  // two adjacent values
-  __device__ static void st2(void* p, int64_t i, int64_t, V a, V b) {
+  // stored words, for kernels that only move them (two adjacent values at a time)
+  using W = V;
+  __device__ static W ldw(const void* p, int64_t i, int64_t) { return ((const double*)p)[i]; }
+  __device__ static void stw(void* p, int64_t i, int64_t, W v) { ((double*)p)[i] = v; }
+  __device__ static void stw2(void* p, int64_t i, int64_t, W a, W b) {
     *reinterpret_cast<d2u*>((double*)p + i) = d2u{a, b};
   }
   __device__ static Acc zero() { return Acc{0.0}; }
@@ -262,7 +265,10 @@ template <> struct Prec<F32> {
   static constexpr int bytes = 4;
   __device__ static V ldc(const void* p, int64_t i, int64_t) { return ((const float*)p)[i]; }
   __device__ static void st(void* p, int64_t i, int64_t, V v) { ((float*)p)[i] = v; }
-  __device__ static void st2(void* p, int64_t i, int64_t, V a, V b) {
+  using W = V;
+  __device__ static W ldw(const void* p, int64_t i, int64_t) { return ((const float*)p)[i]; }
+  __device__ static void stw(void* p, int64_t i, int64_t, W v) { ((float*)p)[i] = v; }
+  __device__ static void stw2(void* p, int64_t i, int64_t, W a, W b) {
     *reinterpret_cast<f2u*>((float*)p + i) = f2u{a, b};
   }
   __device__ static void st_stream(void* p, int64_t i, int64_t plane, V v) { st(p, i, plane, v); }
@@ -297,11 +303,22 @@ template <> struct Prec<F32C> {
     f[i] = h;
     f[plane + i] = (float)(v - (double)h);
   }
-  __device__ static void st2(void* p, int64_t i, int64_t plane, V a, V b) {
+  // (not every pair survives the way through float64: parts further apart than
+  // that, infinities, negative zeros)
+  using W = f2;
+  __device__ static W ldw(const void* p, int64_t i, int64_t plane) {
+    const float* f = (const float*)p;
+    return f2{f[i], f[plane + i]};
+  }
+  __device__ static void stw(void* p, int64_t i, int64_t plane, W v) {
+    float* f = (float*)p;
+    f[i] = v.hi;
+    f[plane + i] = v.lo;
+  }
+  __device__ static void stw2(void* p, int64_t i, int64_t plane, W a, W b) {
     float* f = (float*)p + i;
-    const float ha = (float)a, hb = (float)b;
-    *reinterpret_cast<f2u*>(f) = f2u{ha, hb};
-    *reinterpret_cast<f2u*>(f + plane) = f2u{(float)(a - (double)ha), (float)(b - (double)hb)};
+    *reinterpret_cast<f2u*>(f) = f2u{a.hi, b.hi};
+    *reinterpret_cast<f2u*>(f + plane) = f2u{a.lo, b.lo};
   }
   __device__ static void st_stream(void* p, int64_t i, int64_t plane, V v) { st(p, i, plane, v); }
   __device__ static Acc zero() { return Acc{0.0}; }
