@@ -447,14 +447,14 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
   p->pq.assign(norb + 1, 0);
   p->px2.assign(norb + 1, 0);
   p->pc.assign(norb + 1, 0);
+  int64_t zblocks = 0;   // blocks of kThreads lines along axis 3
   {
-    int64_t blocks = 0;
     int mz = 0;
     for (const OrbDev& d : p->orbs) {
-      blocks += ((int64_t)d.m[0] * d.m[1] + kThreads - 1) / kThreads;
+      zblocks += ((int64_t)d.m[0] * d.m[1] + kThreads - 1) / kThreads;
       mz = std::max(mz, d.m[2]);
     }
-    p->zlen = z_segment_length(blocks, mz);
+    p->zlen = z_segment_length(zblocks, mz);
   }
   for (int b = 0; b < norb; ++b) {
     const OrbDev& d = p->orbs[b];
@@ -482,7 +482,7 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
     for (const OrbDev& d : p->orbs) {
       tiles += ((int64_t)d.m[0] * d.m[1] + 15) / 16 + kZWaves;
       ok = ok && (int64_t)d.m[0] * d.m[1] * d.m[2] < (int64_t)1 << 28 &&
-           (uniform ? line_z_pays(prec, d.m[2]) : line_z_shape(d.m[2]) >= 0);
+           (uniform ? line_z_pays(prec, d.m[2], zblocks) : line_z_shape(d.m[2]) >= 0);
     }
     ok = ok && tiles < (int64_t)1 << 30;
     for (int b = 0; b < norb; ++b) {

@@ -114,23 +114,27 @@ inline int line_z_shape(int m) {
     if (m <= 4 * kZShapes[s].U * kZShapes[s].mi) return s;
   return -1;
 }
-// Whether a uniform batch of lines of m values takes them rather than the
-// strided passes, which read a line's first window twice but leave no lane idle
-// and keep more waves in flight.  Times of the last z step, here / strided:
+// Whether a uniform batch of lines of m values, `blocks` times kThreads of them,
+// takes them rather than the strided passes, which read a line's first window
+// twice but leave no lane idle and keep more waves in flight.  Times of the last
+// z step, here / strided:
 //   float pairs, any length: 0.84 .. 1.0 (W, W^T and K each);
 //   float64: 64 orbitals of 36 x 20 cells and 82 values 118 / 137 us, 98 values
 //   194 / 154; of 56^3 cells 892 / 686;
 //   float32: 64 orbitals of 64^3 points 72 / 80 us, of 80^3 129 / 148; of 72 x 40
 //   planes, 66 values 66 / 54 us, 82 values 75 / 63, 98 values 109 / 72; of
-//   144 x 20 planes and 40 values 52 / 37: seven of eight lanes busy (six for the
-//   shortest shape), and not the shapes of more than 80 values, whose registers
-//   leave fewer waves.
+//   144 x 20 planes, 8 values 29 / 18, 40 values 52 / 37: seven of eight lanes
+//   busy, and not the shapes of more than 80 values, whose registers leave fewer
+//   waves.  The shortest shape also where the strided passes would cut their
+//   lines (H*psi of 200 orbitals of 16^3 points 58 / 62 us; of 40 x 60 x 16,
+//   where they would not, 228 / 208).
 // (Batches of several lengths: 0.9 .. 1.1 either way; they take the classes.)
-inline bool line_z_pays(int prec, int m) {
+inline bool line_z_pays(int prec, int m, int64_t blocks) {
   const int s = line_z_shape(m);
   if (s < 0 || prec == F32C) return s >= 0;
   if (prec == F64) return m <= 96;
-  return m <= 80 && 8 * m >= (s == 0 ? 6 : 7) * 4 * kZShapes[s].U * kZShapes[s].mi;
+  if (s == 0) return m >= 24 || blocks < kZTiles;
+  return m <= 80 && 8 * m >= 7 * 4 * kZShapes[s].U * kZShapes[s].mi;
 }
 
 }  // namespace wvl
