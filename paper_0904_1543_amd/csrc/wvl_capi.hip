@@ -1516,7 +1516,7 @@ int wvl_local_density(wvl_plan* p, const void* c, double* rho, int accumulate, v
   // psi with the combined filter; in-plane passes and the sum over a group's
   // orbitals in the plane kernel where it fits
   WVL_CHK(q.pass(OP_CW, 3, c, A));
-  if (use_line(p) && (p->use_xy || p->use_oz)) {
+  if (use_line(p) && p->use_xy) {
     XyArgs xa = xy_args(p, ws);
     xa.u = A;
     WVL_CHK(line_planes(q, LINE_RHO, xa));

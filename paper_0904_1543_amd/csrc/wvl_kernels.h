@@ -69,11 +69,11 @@ struct CgScal { double alpha, beta, rz, pad; };   // per orbital
 // lines, padded per orbital to the kZWaves of a workgroup; one partial sum per
 // tile.  rows: longest line.
 struct ZLineArgs {
-  const void* in;        // c; ZL_CG: p of the step before (r null: p itself)
+  const void* in;        // c; ZL_CG: p of the step before
   const void* t;         // ZL_FINAL
   const void* k0;        // nullable (not ZL_FINAL's): added
   const void* r;         // ZL_CG
-  void* x;               // ZL_CG, nullable: x += alpha times p of the step before
+  void* x;               // ZL_CG, nullable, not F32: x += alpha times p of the step before
   void* out;
   void* pnew;            // ZL_CG
   const double* eps;

@@ -26,8 +26,7 @@ namespace wvl {
 
 // row pitch of the lines in LDS
 template <int U, typename C> constexpr int zline_pitch() {
-  constexpr int n = kZLines;
-  return sizeof(C) == 8 ? n : n == 64 ? (U == 8 ? 66 : U == 10 ? 72 : 68) : (U == 8 ? 34 : U == 10 ? 40 : 36);
+  return sizeof(C) == 8 ? kZLines : U == 8 ? 66 : U == 10 ? 72 : 68;
 }
 
 template <int P, int U, int MI, int MODE>
@@ -42,7 +41,7 @@ struct ZLine {
   const ZLineArgs& a;
   Lds<C> buf;
   int x, s4;           // lane's line in the tile and first segment
-  int lr, w;           // line that it loads, first row
+  int lr, w;           // line that it loads, first row (the wave)
   uint32_t xl, xr, L;  // line of the orbital that it computes, and that it loads; lines
   int m;
   int64_t off;
@@ -52,8 +51,8 @@ struct ZLine {
       : g(g_), a(a_), buf(b_) {
     const int lane = threadIdx.x & 63;
     x = w_ * 16 + (lane & 15);
-    lr = lane & (kZLines - 1);
-    w = w_ * (64 / kZLines) + lane / kZLines;
+    lr = lane;
+    w = w_;
     s4 = lane >> 4;
     L = (uint32_t)od->m[0] * (uint32_t)od->m[1];
     m = od->m[2];
@@ -136,7 +135,7 @@ struct ZLine {
     if (MODE == ZL_CG) {
       C po[NR];
       load(a.in, po);
-      if (a.x) {
+      if (P != F32 && a.x) {
         load(a.x, r);
         const double al = a.sc[b].alpha;
         uint32_t o = w * L + xr;
@@ -149,30 +148,26 @@ struct ZLine {
             else IO::st_keep(d, o, a.plane, v);
           }
       }
-      if (a.r) {
-        load(a.r, r);
-        // 1 / diag at this lane's parities (rows 4 n + w: w's parity)
-        const uint32_t m1 = (uint32_t)od->m[0], y = xr / m1;
-        const double k0 = (xr - y * m1) & 1 ? od->kdiag[0][1] : od->kdiag[0][0];
-        const double k1 = y & 1 ? od->kdiag[1][1] : od->kdiag[1][0];
-        const double k2 = w & 1 ? od->kdiag[2][1] : od->kdiag[2][0];
-        const double inv = 1.0 / (k0 + k1 + k2 - a.eps[b]), beta = a.sc[b].beta;
-        #pragma unroll
-        for (int n = 0; n < NR; ++n) r[n] = (C)__builtin_fma(beta, (double)po[n], (double)r[n] * inv);
-        uint32_t o = w * L + xr;
-        char* d = IO::at(a.pnew, off);
-        #pragma unroll
-        for (int n = 0; n < NR; ++n, o += 4 * L)
-          if (onr && 4 * n + w < m) {
-            pp = __builtin_fma((double)r[n], (double)r[n], pp);
-            if (P == F64 && g.stream) IO::st(d, o, a.plane, r[n]);
-            else IO::st_keep(d, o, a.plane, r[n]);
-          }
-        wave_total(pp, a.ppart + slot);
-        put(r);
-      } else {
-        put(po);
-      }
+      load(a.r, r);
+      // 1 / diag at this lane's parities (rows 4 n + w: w's parity)
+      const uint32_t m1 = (uint32_t)od->m[0], y = xr / m1;
+      const double k0 = (xr - y * m1) & 1 ? od->kdiag[0][1] : od->kdiag[0][0];
+      const double k1 = y & 1 ? od->kdiag[1][1] : od->kdiag[1][0];
+      const double k2 = w & 1 ? od->kdiag[2][1] : od->kdiag[2][0];
+      const double inv = 1.0 / (k0 + k1 + k2 - a.eps[b]), beta = a.sc[b].beta;
+      #pragma unroll
+      for (int n = 0; n < NR; ++n) r[n] = (C)__builtin_fma(beta, (double)po[n], (double)r[n] * inv);
+      uint32_t o = w * L + xr;
+      char* d = IO::at(a.pnew, off);
+      #pragma unroll
+      for (int n = 0; n < NR; ++n, o += 4 * L)
+        if (onr && 4 * n + w < m) {
+          pp = __builtin_fma((double)r[n], (double)r[n], pp);
+          if (P == F64 && g.stream) IO::st(d, o, a.plane, r[n]);
+          else IO::st_keep(d, o, a.plane, r[n]);
+        }
+      wave_total(pp, a.ppart + slot);
+      put(r);
     } else {
       load(MODE == ZL_FINAL ? a.t : a.in, r);
       put(r);

@@ -104,7 +104,8 @@ enum { ZL_CW = 0, ZL_CWT = 1, ZL_CK = 2, ZL_FINAL = 3, ZL_CG = 4 };
 // segments); the first that fits.  wpe: waves per SIMD that the registers and
 // (last shape) the LDS allow.
 constexpr int kZWaves = 4;   // waves of a workgroup, each 16 lines
-constexpr int kZLines = 16 * kZWaves;
+constexpr int kZLines = 16 * kZWaves;   // a lane loads one of them
+static_assert(kZLines == 64, "a wave loads a row of the tile");
 struct ZShape { int U, mi, wpe; };
 constexpr ZShape kZShapes[] = {{8, 1, 4}, {8, 2, 4}, {10, 2, 3}, {12, 2, 3}, {10, 3, 3},
                                 {12, 3, 2}};
