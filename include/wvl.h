@@ -66,9 +66,10 @@ typedef enum { WVL_F64 = 0, WVL_F32 = 1, WVL_F32C = 2 } wvl_prec;
 /* plan flags */
 #define WVL_SHARED_V   1u  /* all orbitals share one potential (and one grid)   */
 #define WVL_USE_GRAPH  2u  /* record wvl_local_hpsi in a hipGraph and replay it  */
-/* WVL_PERSISTENT: every pass launch of wvl_local_hpsi (y and x passes, z
- * passes of lines longer than 144 values, the per-orbital potential stage and,
- * without WVL_SHARED_V, the in-plane kernel) runs as a persistent launch: a fixed number of workgroups take
+/* WVL_PERSISTENT: the pass launches of wvl_local_hpsi (y and x passes, z
+ * passes that do not hold whole lines in LDS, as those of lines longer than 144
+ * values, the per-orbital potential stage and, without WVL_SHARED_V, the
+ * in-plane kernel) run as persistent launches: a fixed number of workgroups take
  * tiles from a work queue, largest orbitals first (longest-processing-time-
  * first order), which balances batches of uneven orbitals.  The queue
  * counters live in the workspace, so calls that share a workspace must not
@@ -204,8 +205,8 @@ int wvl_decompress(wvl_plan *plan, const void *psi_c, void *c, void *stream);
 /* Step 7 of Sec. 2.4: the region coefficients of c, packed into psi_c. */
 int wvl_compress(wvl_plan *plan, const void *c, void *psi_c, void *stream);
 /* Local Hamiltonian on compressed orbitals, steps 1-7 of Sec. 2.4:
- * decompress into the workspace, wvl_local_hpsi on the whole grid (in place
- * there), compress into hpsi_c, which may be psi_c itself.  The other
+ * decompress into the workspace, wvl_local_hpsi on the whole grid (into another
+ * array there), compress into hpsi_c, which may be psi_c itself.  The other
  * arguments and outputs are those of wvl_local_hpsi (rho and the energies of
  * the decompressed orbitals).  WVL_EUNSUPPORTED without regions. */
 int wvl_local_hpsi_compressed(wvl_plan *plan, const void *psi_c, const double *V,
@@ -314,8 +315,10 @@ int wvl_plan_sync(wvl_plan *plan, void *stream);
  * group's plane in LDS; WVL_NO_RHO_LDS keeps it in memory),
  * WVL_EXACT_OCCUPANCY_Z=2 the last z kernel of the digit products for 2, and
  * WVL_NO_ZFUSE runs the last z step as two passes instead of one fused
- * launch (same results bit for bit; the fused launch is used for WVL_F64,
- * WVL_F32 and variant 3).)  With WVL_AUTOTUNE, times_ms[k] (k < ntimes, at most 15
+ * launch; so does a call in place.  The results are the same bit for bit in
+ * WVL_F64 and WVL_F32; for float pairs the two passes round K_z c + kxy to a pair
+ * in between, which the fused launch keeps in float64.  The fused launch is used
+ * for WVL_F64, WVL_F32 and variant 3 (except the digit products).)  With WVL_AUTOTUNE, times_ms[k] (k < ntimes, at most 15
  * candidates) receives the mean time of candidate k = 3 seq + shape, or -1
  * where it was not available:
  *   seq 0 one pass per axis; 1 the plane kernel (workgroup-wide at 4 waves per

@@ -122,7 +122,7 @@ struct wvl_plan {
   // as ranges of perm_q / order_q; none if some plane is too large for it
   struct LineClass { int first, n, m1, m2, tiles; };
   std::vector<LineClass> line_cls;
-  bool zfuse = true;   // last two z passes of the plane path fused (not for F32C)
+  bool zfuse = true;   // last two z passes of the plane path fused (F32C: variant 3 only)
   // compensated uniform plans, lengths multiples of 16, isotropic grid spacing
   // (variant 3 with a shared potential, preconditioner form 2)
   bool pairs_iso = false;
@@ -522,9 +522,12 @@ int wvl_plan_create(wvl_ctx* ctx, const wvl_orbital* orbs, int32_t norb, int32_t
   // Variant 3 of the compensated form.  Planes with a shape of the plane kernel
   // take it, with the last z step fused: float64 arithmetic on the pairs is
   // faster than their exact digit products on the matrix cores (256 orbitals of
-  // 48^3 cells: H*psi 5.22 ms against 6.61; error against float64 8e-16 against
-  // 3e-10).  The digit products keep the longer rows, where the other choice
-  // is one pass per axis.
+  // 48^3 cells: H*psi 5.22 ms against 6.61; normwise error of hi + lo 1.0e-15
+  // against 1.1e-12).  The digit products keep the longer rows, where the other
+  // choice is the workgroup-wide kernel (16 orbitals of 144 x 64 x 32 points 180
+  // us against 306).  Pair plans outside this variant run the last z step as two
+  // passes, as they did before the fused kernel held pairs; the fused step itself
+  // needs neither these lengths nor equal spacings.
   {
     bool ok = prec == WVL_F32C && uniform && !p->bc_any && !getenv("WVL_F32C_VECTOR") &&
               !getenv("WVL_NO_PLANE_KERNEL");
