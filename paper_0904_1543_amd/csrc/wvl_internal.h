@@ -135,7 +135,7 @@ struct PassGeom {
 // Outputs per lane of the axis-3 passes of a batch with `tiles` blocks of
 // kThreads whole lines, the longest of m values.  A lane runs down its line one
 // pair after the other, so a small batch waits for a few long chains (of lines
-// too long for wvl_line_z.h): it is cut
+// that wvl_line_z.h does not take): it is cut
 // until there are two workgroups per compute unit (what the registers of the
 // last z step let it hold), each lane reading the filter's reach on both sides
 // of its segment again.  One orbital of 16^3 cells: z pass 10 -> 6 us, last z

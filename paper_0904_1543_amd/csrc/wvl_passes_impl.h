@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kThreads) void k_zfinal(PassGeom g, const void* __r
 // (4.7 TB/s) where the two took 0.93 + 1.02.  p goes to another
 // array than p_old: lanes re-read the ends of a line for the periodic wrap.
 // Loads, not the FMAs, bound it: kPfP pairs of each operand are in flight.
-// (Lines of up to 144 values: wvl_line_z.h.)
+// (Lines held in LDS: wvl_line_z.h.)
 // ---------------------------------------------------------------------------
 constexpr int kPfP = 2;
 

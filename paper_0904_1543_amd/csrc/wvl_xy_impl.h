@@ -1,6 +1,7 @@
 // The in-plane part of the local Hamiltonian, one z-plane per workgroup, every
 // pass over the whole workgroup, gfx950: the form for planes that the kernel
-// of wvl_line.h does not hold (a side of more than 128 values), and the
+// of wvl_line.h does not hold (a side of more than 128 values), for the
+// preconditioner's operator on batches of several medium grids, and the
 // alternative engines.
 //
 // The 3D operators are tensor products of 1D operators (Sec. 3.1), so the
